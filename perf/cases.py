@@ -637,13 +637,13 @@ def work(case):
 def tolerance(case):
     """About four times what the passes show against exact() and between two runs (vertex order, and with it the
     order of sums, changes from run to run)."""
-    if case["op"] == "pointnet" and case["train"]:      # near ties of the maximum: 7.7e-4 against 64 bits
-        return {"rel": 3e-3}
+    if case["op"] == "pointnet" and case["train"]:      # near ties of the maximum: 1.3e-3 against 64 bits
+        return {"rel": 5e-3}
     deform = case["op"] == "head" or case["tail"] == "deform"
     if case["op"] != "head" and deform and case["train"]:
         # which vertex wins the maximum follows from rounded rows: a flip moves a whole gradient term
-        # (2.7e-2 against 64 bits with 16-bit rows, 3.2e-4 with 32-bit ones)
-        return {"rel": 0.1 if case["dtype"] == "bf16" else 1.3e-3}
+        # (2.7e-2 against 64 bits with 16-bit rows, 9.2e-4 with 32-bit ones)
+        return {"rel": 0.1 if case["dtype"] == "bf16" else 4e-3}
     if case["dtype"] == "bf16":                         # 3.4e-3
         return {"rel": 1.5e-2}
     if deform and case["train"]:                        # one flip in a small cloud
