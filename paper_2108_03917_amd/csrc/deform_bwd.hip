@@ -826,8 +826,7 @@ hipError_t run_d(lattice *L, const void *values, bool in_bf16, int C, const floa
                                                 reinterpret_cast<float *>(scratch + l.part), grad_values)) != hipSuccess)
         return e;
     float *tmp = reinterpret_cast<float *>(scratch + l.tmp);
-    if (grad_w_delta && (e = rowsum::sum(L->stream, pw, nwaves, C, tmp, grad_w_delta)) != hipSuccess) return e;
-    if (grad_b_delta && (e = rowsum::sum(L->stream, pb, nwaves, 1, tmp, grad_b_delta)) != hipSuccess) return e;
+    rowsum::Job jobs[4] = {{pw, grad_w_delta, nwaves, C}, {pb, grad_b_delta, nwaves, 1}, {}, {}};
     if (w_cls && (grad_w_cls || grad_b_cls)) {
         float *pc = reinterpret_cast<float *>(scratch + l.pc);
         float *pbc = reinterpret_cast<float *>(scratch + l.pbc);
@@ -835,11 +834,11 @@ hipError_t run_d(lattice *L, const void *values, bool in_bf16, int C, const floa
         hipLaunchKernelGGL(k_dfb_cls, dim3((unsigned)((nch + kBlock / 64 - 1) / (kBlock / 64)), tiles), dim3(kBlock), 0,
                            L->stream, L->m, nch, C, n_cls, grad_out, f, pc, pbc);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (grad_w_cls && (e = rowsum::sum(L->stream, pc, nch, (int64_t)n_cls * C, tmp, grad_w_cls)) != hipSuccess)
-            return e;
-        if (grad_b_cls && (e = rowsum::sum(L->stream, pbc, nch, n_cls, tmp, grad_b_cls)) != hipSuccess) return e;
+        jobs[2] = {pc, grad_w_cls, nch, (int64_t)n_cls * C};
+        jobs[3] = {pbc, grad_b_cls, nch, n_cls};
     }
-    return hipSuccess;
+    // every gradient's partial rows in one launch
+    return rowsum::sum_all(L->stream, jobs, 4, tmp);
 }
 
 }  // namespace

@@ -1774,8 +1774,8 @@ hipError_t launch_distribute_backward(lattice *L, const float *pos, const float 
     if ((e = batched ? back(k_dpn_back<1, true>, 0, F(l.d2), nullptr, l.pb1)
                    : back(k_dpn_back<1, false>, 0, F(l.d2), nullptr, l.pb1)) != hipSuccess)
         return e;
-    if ((e = reduce(F(l.pb1), l.nwaves, kPB1, F(l.r1))) != hipSuccess) return e;
-    if ((e = reduce(F(l.parg), l.nwaves_arg, kPArg, F(l.rarg))) != hipSuccess) return e;
+    const rowsum::Job last[2] = {{F(l.pb1), F(l.r1), l.nwaves, kPB1}, {F(l.parg), F(l.rarg), l.nwaves_arg, kPArg}};
+    if ((e = rowsum::sum_all(L->stream, last, 2, F(l.tmp))) != hipSuccess) return e;
     hipLaunchKernelGGL(k_dpn_out, dim3(16), dim3(kBlock), 0, L->stream, F(l.r1), F(l.r2), F(l.r3), F(l.rarg), k0,
                        grad_params);
     return hipGetLastError();
