@@ -22,8 +22,9 @@
 // persistent: V lives on the device, so the grid is sized for the largest
 // lattice and every workgroup reads V and strides over the tiles.
 //
-// k_conv_any: MFMA over any channel counts and alignments (e.g. 8 -> 16),
-// with the operands gathered element by element.
+// k_conv_any: MFMA over any channel counts and alignments, with the operands
+// gathered element by element: what the kernels here and k_conv_seg
+// (conv_seg.hip) do not cover (C_in not a multiple of 4, unaligned operands).
 #include <type_traits>
 
 #include "internal.h"
@@ -1045,9 +1046,9 @@ __global__ __launch_bounds__(256) void k_conv_ring(const void *__restrict__ in_,
 }
 
 // Any shape and any storage/compute combination on MFMA: the fallback for
-// channel counts the tilings above do not cover (C_in or C_out not a
-// multiple of 32 / 64, e.g. 8 -> 16), and for operands that are not 16-byte
-// aligned.  The product is the same Y = Z W^T over the flattened
+// channel counts that neither the tilings above nor k_conv_seg cover (C_in
+// not a multiple of 4), for bf16 rows with fp32 weights, and for operands
+// that are not 16-byte aligned.  The product is the same Y = Z W^T over the flattened
 // K = T C_in: a workgroup of WM x WN wavefronts owns a (32 WM) x (32 WN)
 // output tile, each wavefront one 32 x 32 MFMA block.  K is walked in
 // chunks of KC = 64: every thread gathers its share of the chunk's
@@ -1388,6 +1389,22 @@ hipError_t dispatch_out(lattice *L, const void *in, lattice_dtype in_dt, int C_i
     // wavefronts) only on request; the LDS-tiled kernel is faster there
     if (aligned && out_vec && path == LATTICE_CONV_RS && !bf16 && !in_bf16 && L->T == 9 && C_in == 64 && C_out == 64)
         return launch_rs<false, OUT_BF16, 9, 64, 64, 2>(L, in, w, bias, out);
+    // Of the other shapes, the segment-walking kernel takes (AUTO) every bf16
+    // one but 64 -> a multiple of 128 with 9 taps, where the resident weight
+    // slice is a little faster (64 -> 256, us, V = 24 941 / 70 989 / 278 788:
+    // 22.6 / 57.8 / 187 against 26.7 / 56.1 / 198; elsewhere e.g. 128 -> 64 on
+    // V = 70 989 41 against 27, fp32 rows 64 -> 64 47 against 31), the fp32
+    // ones the LDS-tiled kernel is not built for, and fp32 -> 64 channels on
+    // small clouds, whose 64-row tiles leave CUs idle (64 -> 64 on V = 5 211:
+    // 17.0 against 12.9; larger: 58.6 against 60.2)
+    const bool seg = aligned && conv_seg_covers(in_dt, C_in, dt);
+    const lattice_dtype out_dt = OUT_BF16 ? LATTICE_BF16 : LATTICE_F32;
+    const bool small = L->max_vertices <= 64 * (int64_t)L->cu_count;
+    if (seg && path == LATTICE_CONV_AUTO) {
+        const bool ws = in_bf16 && L->T == 9 && C_in == 64 && C_out % 128 == 0;
+        const bool tiled = C_in % 32 == 0 && C_out % 64 == 0 && !(small && C_out == 64);
+        if (bf16 ? !ws : !tiled) return launch_conv_seg(L, in, in_dt, C_in, w, C_out, dt, bias, out, out_dt);
+    }
     if (aligned && path != LATTICE_CONV_TILED) {
         hipError_t err = hipSuccess;
         if (try_ws<OUT_BF16>(L, in, in_bf16, C_in, w, C_out, bf16, bias, out, &err)) return err;
@@ -1400,6 +1417,7 @@ hipError_t dispatch_out(lattice *L, const void *in, lattice_dtype in_dt, int C_i
         if (bf16 && in_bf16 && C_in % 64 == 0)
             return launch_mfma_n<2, OUT_BF16>(L, in, C_in, w, C_out, bias, out);
     }
+    if (seg) return launch_conv_seg(L, in, in_dt, C_in, w, C_out, dt, bias, out, out_dt);
     if (in_bf16)
         return bf16 ? launch_any<true, true, OUT_BF16>(L, in, C_in, w, C_out, bias, out)
                     : launch_any<true, false, OUT_BF16>(L, in, C_in, w, C_out, bias, out);

@@ -1,0 +1,336 @@
+// 1-hop-ring lattice convolution for channel counts that the resident-weight
+// kernels of conv.hip are not built for (e.g. 8 -> 16, 32, 48, 96, 100
+// channels): Y[V x C_out] = Z[V x K] W^T over the flattened K = T C_in, row v
+// of Z being the concatenation of the T neighbour rows of v.
+//
+// Both sides are walked in segments of SE consecutive channels that never
+// cross a tap: a tap has ceil(C_in / SE) of them, and segment s of a row is
+// the s-th of all its taps'.  K has no padding beyond that (C_in is a multiple
+// of SE, or, for bf16 rows, of SE / 2: then the last segment of a tap loads
+// the tap's last SE channels and keeps the upper half), and every load is one
+// 16-byte access, the lanes of a row's chunk reading consecutive segments.
+//
+// A workgroup of four wavefronts owns a BM x BN output tile, BN the whole of
+// C_out up to 128, so that a neighbour row is gathered once per tap.  Chunks
+// of 128 LDS bytes per row (64 bf16 or 32 fp32 of K) go through a register
+// ring of two chunks into two LDS buffers, one barrier a chunk.  Rows are
+// padded to 144 bytes: 16 rows read 16 bytes each on 64 different banks.
+// The product runs on MFMA 16x16 (16x16x32 bf16, 16x16x4 fp32) with the
+// weights as the A operand, so that a lane ends up with four consecutive
+// output channels of one row and stores them at once.
+//
+// What bounds it: bf16, the gathers and the weight rows through L2 (each tile
+// re-reads W); fp32, the matrix cores (90 of 154 TFLOP/s).  Against the
+// element-wise kernel that took these shapes before (us, before -> now):
+// V = 278 788, 9 taps: bf16 32 -> 32 115 -> 30, 96 -> 96 546 -> 109, 100 -> 100
+// 583 -> 159, fp32 96 -> 96 963 -> 522, 8 -> 16 90 -> 24; V = 24 941: fp32
+// 96 -> 96 114 -> 56.
+#include <type_traits>
+
+#include "internal.h"
+
+namespace {
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+
+constexpr int kRowBytes = 144;
+constexpr int kMaxTaps = LATTICE_TAPS(LATTICE_MAX_D);
+constexpr int kThreads = 256;
+
+// CM 0: fp32 rows and weights, fp32 MFMA; CM 1: fp32 rows rounded to bf16
+// while staging, bf16 weights; CM 2: bf16 rows and weights.  The four
+// wavefronts are WM x (4 / WM), each TI x TJ tiles of 16 x 16.
+template <int CM, int WM, int TI, int TJ>
+__global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ in, int C_in,
+                                                       const void *__restrict__ wv, int C_out, int T,
+                                                       const float *__restrict__ bias, void *__restrict__ out,
+                                                       int out_bf16, int out_vec, const int32_t *__restrict__ nbr,
+                                                       const int32_t *__restrict__ counters) {
+    constexpr int WN = 4 / WM;
+    constexpr int BM = WM * TI * 16, BN = WN * TJ * 16;
+    constexpr int SE = CM == 2 ? 8 : 4;               // channels per segment
+    constexpr int ESZ = CM == 0 ? 4 : 2;              // operand element in LDS
+    constexpr int SB = SE * ESZ;                      // LDS (and weight) bytes per segment
+    constexpr int XESZ = CM == 2 ? 2 : 4;             // stored input element: 16 bytes of input per segment
+    constexpr int SEGS = 128 / SB;                    // segments per row and chunk
+    constexpr int RPP = kThreads / SEGS;              // rows per pass
+    constexpr int AP = (BM + RPP - 1) / RPP, BP = (BN + RPP - 1) / RPP;
+    constexpr int AR = AP * RPP, BR = BP * RPP;       // LDS rows (whole passes)
+    constexpr int P = 2;                              // chunks in the register ring
+    typedef u32x4_t xseg_t;
+    typedef typename std::conditional<SB == 16, u32x4_t, u32x2_t>::type wseg_t;
+
+    __shared__ __attribute__((aligned(16))) char lds[2 * (AR + BR) * kRowBytes];
+    __shared__ int32_t nbr_s[AR * kMaxTaps];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / WN, wn = wave % WN;
+    const int j16 = lane & 15, q4 = lane >> 4;
+    const int seg = tid % SEGS, row0 = tid / SEGS;
+    const int64_t V = counters[CNT_V];
+    const int64_t n_mt = (V + BM - 1) / BM;
+    const int n_nt = (C_out + BN - 1) / BN;
+    const int spr = (C_in + SE - 1) / SE;             // segments per tap
+    const bool half = C_in % SE != 0;                 // the last one of a tap is its upper half
+    const int64_t K = (int64_t)T * C_in;
+    const int NS = T * spr;                           // segments of a whole row
+    const int NQ = (NS + SEGS - 1) / SEGS;
+
+    for (int64_t tile = blockIdx.x; tile < n_mt * n_nt; tile += gridDim.x) {
+        const int64_t row_base = (tile / n_nt) * BM;
+        const int col_base = (int)(tile % n_nt) * BN;
+        for (int i = tid; i < AR * T; i += kThreads) {
+            const int64_t e = row_base * T + i;
+            nbr_s[i] = (i < BM * T && e < V * T) ? nbr[e] : -1;
+        }
+        __syncthreads();
+
+        f32x4_t acc[TI][TJ];
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+        xseg_t areg[P][AP];
+        wseg_t breg[P][BP];
+        uint32_t mask[P];  // bit i: row pass i present; bit 15 + i: weight pass i inside; bit 31: half
+        int lt = 0, lc = seg;  // this thread's next segment: tap, segment of the tap
+        while (lc >= spr) {
+            lc -= spr;
+            ++lt;
+        }
+        // Branch-free loads of the next chunk into ring slot s: an absent
+        // neighbour, a segment past K and a column past C_out read row 0 and
+        // are zeroed when they go to LDS.  Past the last chunk the slot's
+        // loads are those of row 0 and nobody uses them.
+        auto load_chunk = [&](int s) {
+            const bool in_k = lt < T;
+            uint32_t mk = 0;
+            const int t = in_k ? lt : 0;
+            int c = in_k ? lc * SE : 0;  // first channel loaded
+            if (CM == 2 && half && c + SE > C_in) {
+                c = C_in - SE;
+                mk = 1u << 31;
+            }
+#pragma unroll
+            for (int i = 0; i < AP; ++i) {
+                const int u = nbr_s[(row0 + i * RPP) * T + t];
+                if (in_k && u >= 0) mk |= 1u << i;
+                const int64_t row = u >= 0 ? u : 0;
+                areg[s][i] = *reinterpret_cast<const xseg_t *>(reinterpret_cast<const char *>(in) +
+                                                              (row * C_in + c) * XESZ);
+            }
+#pragma unroll
+            for (int i = 0; i < BP; ++i) {
+                const int n = col_base + row0 + i * RPP;
+                const bool ok = in_k && n < C_out && row0 + i * RPP < BN;
+                if (ok) mk |= 1u << (15 + i);
+                breg[s][i] = *reinterpret_cast<const wseg_t *>(reinterpret_cast<const char *>(wv) +
+                                                              ((ok ? n : 0) * K + t * C_in + c) * ESZ);
+            }
+            mask[s] = mk;
+            lc += SEGS;
+            while (lc >= spr) {
+                lc -= spr;
+                ++lt;
+            }
+        };
+        auto store_chunk = [&](int s, int buf) {
+            const bool hi = CM == 2 && (mask[s] >> 31);
+            char *A = lds + buf * (AR + BR) * kRowBytes;
+            char *B = A + AR * kRowBytes;
+#pragma unroll
+            for (int i = 0; i < AP; ++i) {
+                const bool on = (mask[s] >> i) & 1u;
+                wseg_t y;
+                if constexpr (CM == 1) {
+                    const xseg_t x = areg[s][i];
+                    y[0] = bf16_bits(__uint_as_float(x[0])) | (bf16_bits(__uint_as_float(x[1])) << 16);
+                    y[1] = bf16_bits(__uint_as_float(x[2])) | (bf16_bits(__uint_as_float(x[3])) << 16);
+                } else {
+                    y = areg[s][i];
+                    if constexpr (CM == 2) y = hi ? u32x4_t{y[2], y[3], 0u, 0u} : y;
+                }
+#pragma unroll
+                for (int k = 0; k < SB / 4; ++k) y[k] = on ? y[k] : 0u;
+                *reinterpret_cast<wseg_t *>(A + (row0 + i * RPP) * kRowBytes + seg * SB) = y;
+            }
+#pragma unroll
+            for (int i = 0; i < BP; ++i) {
+                const bool on = (mask[s] >> (15 + i)) & 1u;
+                wseg_t y = breg[s][i];
+                if constexpr (CM == 2) y = hi ? u32x4_t{y[2], y[3], 0u, 0u} : y;
+#pragma unroll
+                for (int k = 0; k < SB / 4; ++k) y[k] = on ? y[k] : 0u;
+                *reinterpret_cast<wseg_t *>(B + (row0 + i * RPP) * kRowBytes + seg * SB) = y;
+            }
+        };
+        // lane quarter q holds bytes 16 q .. of each 64: the same K in A and B
+        auto compute = [&](int buf) {
+            const char *A = lds + buf * (AR + BR) * kRowBytes + (wm * TI * 16 + j16) * kRowBytes + 16 * q4;
+            const char *B = lds + buf * (AR + BR) * kRowBytes + (AR + wn * TJ * 16 + j16) * kRowBytes + 16 * q4;
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                u32x4_t a[TI], b[TJ];
+#pragma unroll
+                for (int i = 0; i < TI; ++i)
+                    a[i] = *reinterpret_cast<const u32x4_t *>(A + i * 16 * kRowBytes + 64 * g);
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+                    b[j] = *reinterpret_cast<const u32x4_t *>(B + j * 16 * kRowBytes + 64 * g);
+                if constexpr (CM == 0) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+#pragma unroll
+                        for (int i = 0; i < TI; ++i)
+#pragma unroll
+                            for (int j = 0; j < TJ; ++j)
+                                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                    __uint_as_float(b[j][c]), __uint_as_float(a[i][c]), acc[i][j], 0, 0, 0);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < TI; ++i)
+#pragma unroll
+                        for (int j = 0; j < TJ; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, b[j]),
+                                                                                __builtin_bit_cast(bf16x8_t, a[i]),
+                                                                                acc[i][j], 0, 0, 0);
+                }
+            }
+        };
+
+        // ring slot s holds chunk s mod 2; LDS buffer s holds it while it is multiplied
+        load_chunk(0);
+        load_chunk(1);
+        store_chunk(0, 0);
+        __syncthreads();
+        const int NQP = NQ / 2 * 2;
+        for (int q = 0; q < NQP; q += 2) {
+            load_chunk(0);
+            compute(0);
+            store_chunk(1, 1);
+            __syncthreads();
+            load_chunk(1);
+            compute(1);
+            store_chunk(0, 0);
+            __syncthreads();
+        }
+        if (NQ & 1) {
+            compute(0);
+            __syncthreads();  // the LDS is rewritten by the next tile
+        }
+
+        // register r of lane (j16, q4): row j16, column 4 q4 + r of each tile
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
+            const int64_t row = row_base + (wm * TI + i) * 16 + j16;
+            if (row >= V) continue;
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                const int col = col_base + (wn * TJ + j) * 16 + 4 * q4;
+                f32x4_t y = acc[i][j];
+                if (bias) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) y[r] += col + r < C_out ? bias[col + r] : 0.f;
+                }
+                const int64_t at = row * C_out + col;
+                if (out_vec) {  // C_out a multiple of 4, rows aligned for it
+                    if (col >= C_out) continue;
+                    if (out_bf16) {
+                        u32x2_t pk;
+                        pk[0] = bf16_bits(y[0]) | (bf16_bits(y[1]) << 16);
+                        pk[1] = bf16_bits(y[2]) | (bf16_bits(y[3]) << 16);
+                        *reinterpret_cast<u32x2_t *>(reinterpret_cast<uint16_t *>(out) + at) = pk;
+                    } else {
+                        *reinterpret_cast<f32x4_t *>(reinterpret_cast<float *>(out) + at) = y;
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (col + r >= C_out) continue;
+                        if (out_bf16) reinterpret_cast<uint16_t *>(out)[at + r] = (uint16_t)bf16_bits(y[r]);
+                        else reinterpret_cast<float *>(out)[at + r] = y[r];
+                    }
+                }
+            }
+        }
+    }
+}
+
+template <int CM, int WM, int TI, int TJ>
+hipError_t go(lattice *L, const void *in, int C_in, const void *w, int C_out, const float *bias, void *out,
+              bool out_bf16, bool out_vec) {
+    constexpr int BM = WM * TI * 16, BN = (4 / WM) * TJ * 16;
+    const int64_t tiles = ((L->max_vertices + BM - 1) / BM) * ((C_out + BN - 1) / BN);
+    int64_t grid = (int64_t)L->cu_count * 4;
+    if (grid > tiles) grid = tiles;
+    if (grid < 1) grid = 1;
+    hipLaunchKernelGGL((k_conv_seg<CM, WM, TI, TJ>), dim3((unsigned)grid), dim3(kThreads), 0, L->stream, in, C_in,
+                       w, C_out, L->T, bias, out, out_bf16 ? 1 : 0, out_vec ? 1 : 0, L->nbr, L->counters);
+    return hipGetLastError();
+}
+
+// The tile's width: of 16, 32, 48 (four wavefronts along the rows) and 64,
+// 96, 128 (two by two) the one that costs least, a tile costing its columns
+// and the gather of its rows, about as much as 64 columns.
+int tile_width(int C_out) {
+    static const int w[6] = {128, 96, 64, 48, 32, 16};
+    int best = 128, cost = 1 << 30;
+    for (int n : w) {
+        const int c = (C_out + n - 1) / n * (n + 64);
+        if (c < cost) {
+            cost = c;
+            best = n;
+        }
+    }
+    return best;
+}
+
+template <int CM, int M4, int M2>
+hipError_t by_width(lattice *L, const void *in, int C_in, const void *w, int C_out, const float *bias, void *out,
+                    bool out_bf16, bool out_vec) {
+    switch (tile_width(C_out)) {
+        case 16: return go<CM, 4, M4, 1>(L, in, C_in, w, C_out, bias, out, out_bf16, out_vec);
+        case 32: return go<CM, 4, M4, 2>(L, in, C_in, w, C_out, bias, out, out_bf16, out_vec);
+        case 48: return go<CM, 4, M4, 3>(L, in, C_in, w, C_out, bias, out, out_bf16, out_vec);
+        case 64: return go<CM, 2, M2, 2>(L, in, C_in, w, C_out, bias, out, out_bf16, out_vec);
+        case 96: return go<CM, 2, M2, 3>(L, in, C_in, w, C_out, bias, out, out_bf16, out_vec);
+        default: return go<CM, 2, M2, 4>(L, in, C_in, w, C_out, bias, out, out_bf16, out_vec);
+    }
+}
+
+}  // namespace
+
+bool conv_seg_covers(lattice_dtype in_dt, int C_in, lattice_dtype dt) {
+    if (dt == LATTICE_F32) return in_dt == LATTICE_F32 && C_in % 4 == 0;
+    return C_in % 4 == 0 && (in_dt == LATTICE_F32 || C_in >= 8);
+}
+
+hipError_t launch_conv_seg(lattice *L, const void *in, lattice_dtype in_dt, int C_in, const void *w, int C_out,
+                           lattice_dtype dt, const float *bias, void *out, lattice_dtype out_dt) {
+    const bool ob = out_dt == LATTICE_BF16;
+    const bool vec = C_out % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & (ob ? 7 : 15)) == 0;
+    // Rows per tile (V is on the device: the lattice's bound stands for it).
+    // Clouds whose bound gives fewer tiles of 64 rows than CUs take half
+    // tiles (one part-segmentation object, V = 5 211, us: bf16 64 -> 96 8.7
+    // against 7.8, fp32 96 -> 96 32.8 against 22.5); 96-wide tiles of large
+    // lattices take 128 rows, which halves the weight reads (bf16 96 -> 96 on
+    // V = 278 788: 131 against 109, on V = 143 537: 74 against 68; on
+    // V = 70 989 35 against 38, so from 400 000 on).
+    const bool small = L->max_vertices <= 64 * (int64_t)L->cu_count;
+    if (dt == LATTICE_F32) {
+        if (small) return by_width<0, 1, 1>(L, in, C_in, w, C_out, bias, out, ob, vec);
+        return by_width<0, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
+    }
+    if (in_dt == LATTICE_F32) {
+        if (small) return by_width<1, 1, 1>(L, in, C_in, w, C_out, bias, out, ob, vec);
+        return by_width<1, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
+    }
+    if (small) return by_width<2, 1, 1>(L, in, C_in, w, C_out, bias, out, ob, vec);
+    if (tile_width(C_out) == 96 && L->max_vertices >= 400000)
+        return go<2, 2, 4, 3>(L, in, C_in, w, C_out, bias, out, ob, vec);
+    return by_width<2, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
+}

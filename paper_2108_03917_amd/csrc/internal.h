@@ -171,6 +171,11 @@ hipError_t launch_cross(lattice *out, const lattice *src, bool up, int32_t *xnbr
 hipError_t launch_conv(lattice *L, const void *in, lattice_dtype in_dt, int C_in, const void *w, int C_out,
                        lattice_dtype dt, const float *bias, void *out, lattice_dtype out_dt);
 
+// conv_seg.hip: any C_in that is a multiple of 4 (16-byte aligned operands)
+bool conv_seg_covers(lattice_dtype in_dt, int C_in, lattice_dtype dt);
+hipError_t launch_conv_seg(lattice *L, const void *in, lattice_dtype in_dt, int C_in, const void *w, int C_out,
+                           lattice_dtype dt, const float *bias, void *out, lattice_dtype out_dt);
+
 // slice.hip
 hipError_t launch_slice(lattice *L, const void *values, lattice_dtype values_dt, int C, float *out);
 hipError_t launch_splat_backward(lattice *L, const void *grad_values, lattice_dtype gv_dt, int C,

@@ -759,3 +759,34 @@ def test_splat_large_cloud_insert_paths(d, ordered, batched):
     ref, wref, scale = O.splat(lat, feat)
     assert_close_scaled(g.values(), ref, scale, REL_F32, "large-cloud splat")
     assert_close_scaled(g.weight(), wref, wref, REL_F32, "large-cloud weight")
+
+
+@pytest.mark.parametrize("C_in,C_out,in_dtype,dtype", [
+    (8, 16, "f32", "f32"), (12, 1, "f32", "f32"), (4, 17, "f32", "f32"), (96, 96, "f32", "f32"),
+    (36, 49, "f32", "f32"), (100, 130, "f32", "f32"), (64, 64, "f32", "f32"),
+    (8, 33, "bf16", "bf16"), (12, 48, "bf16", "bf16"), (100, 100, "bf16", "bf16"), (36, 97, "bf16", "bf16"),
+    (96, 96, "bf16", "bf16"), (128, 192, "bf16", "bf16"), (20, 112, "f32", "bf16"), (64, 64, "f32", "bf16"),
+    (4, 31, "f32", "bf16")])
+@pytest.mark.parametrize("d,m", [(3, 1), (3, 700), (4, 700), (3, 70000), (4, 90000)])
+def test_conv_segment_shapes(C_in, C_out, in_dtype, dtype, d, m):
+    """Channel counts off the tile sizes (a tap's last segment half full, a
+    partly empty last chunk and column tile), at every row-tile size: one
+    row, a ragged tile, a lattice whose bound takes whole and double tiles."""
+    w = random_cloud(m, d, seed=1200 + d, extent=1.0, C=1)
+    L = _lattice(d, 0.6, w.m)
+    g = GpuLattice(L, w.pos, w.feat)
+    lat = O.build(w.pos, 0.6)
+    nbr = O.neighbors(lat)
+    x = random_rows(lat.V, C_in, seed=1210)
+    W = conv_weight(C_in, C_out, d, seed=1211)
+    b = random_rows(1, C_out, seed=1212)[0]
+    xin, wd = g.to_gpu_order(x), to_dev(W)
+    if dtype == "bf16":
+        x, W, wd = O.round_bf16(x), O.round_bf16(W), L.weights_to_bf16(wd)
+        xin = xin.to(torch.bfloat16) if in_dtype == "bf16" else xin
+    ref, scale = O.conv(x.astype(np.float64), nbr, W.astype(np.float64), b)
+    for out_dtype in ("f32", "bf16"):
+        got = g.from_gpu_order(L.conv(xin, wd, dtype=dtype, bias=to_dev(b), out_dtype=out_dtype).float())
+        tol = REL_F32 * scale + (BF16_ULP * np.abs(ref) if out_dtype == "bf16" else 0.0)
+        assert_close_scaled(got, ref, tol, 1.0, f"{in_dtype} rows {dtype} conv {C_in}x{C_out} d={d} out {out_dtype}")
+    L.close()
