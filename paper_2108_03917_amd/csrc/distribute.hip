@@ -561,6 +561,48 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// h_0 = [g_p - mu_v ; f_p] of one entry, zero-padded (all zero when not
+// valid; then v and p need not be an entry's).  pos4: d = 4 with 16-byte
+// aligned rows.
+__device__ __forceinline__ bool pos_rows16(const float *pos, const float *mu, int d) {
+    return d == 4 && ((reinterpret_cast<uintptr_t>(pos) | reinterpret_cast<uintptr_t>(mu)) & 15) == 0;
+}
+__device__ __forceinline__ void load_h0(bool valid, int v, int p, const float *__restrict__ pos,
+                                        const float *__restrict__ mu, const float *__restrict__ feat, int d, int f_d,
+                                        bool pos4, float *x) {
+    const int k0 = d + f_d;
+    if (pos4) {
+        // the position and the mean as one 16-byte load each
+        const float4 pp = valid ? reinterpret_cast<const float4 *>(pos)[p] : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 mm = valid ? reinterpret_cast<const float4 *>(mu)[v] : make_float4(0.f, 0.f, 0.f, 0.f);
+        x[0] = pp.x - mm.x;
+        x[1] = pp.y - mm.y;
+        x[2] = pp.z - mm.z;
+        x[3] = pp.w - mm.w;
+#pragma unroll
+        for (int i = 4; i < kMaxK0; ++i) x[i] = valid && i < k0 ? feat[(int64_t)p * f_d + (i - 4)] : 0.f;
+    } else if (d == 3) {
+        // three adjacent 4-byte loads each (unconditional, so that they merge
+        // into one 12-byte load)
+        const int64_t p3 = (int64_t)(valid ? p : 0) * 3, v3 = (int64_t)(valid ? v : 0) * 3;
+        const float p0 = pos[p3], p1 = pos[p3 + 1], p2 = pos[p3 + 2];
+        const float m0 = mu[v3], m1 = mu[v3 + 1], m2 = mu[v3 + 2];
+        x[0] = valid ? p0 - m0 : 0.f;
+        x[1] = valid ? p1 - m1 : 0.f;
+        x[2] = valid ? p2 - m2 : 0.f;
+#pragma unroll
+        for (int i = 3; i < kMaxK0; ++i) x[i] = valid && i < k0 ? feat[(int64_t)p * f_d + (i - 3)] : 0.f;
+    } else {
+#pragma unroll
+        for (int i = 0; i < kMaxK0; ++i) {
+            float t = 0.f;
+            if (valid && i < d) t = pos[(int64_t)p * d + i] - mu[(int64_t)v * d + i];
+            else if (valid && i < k0) t = feat[(int64_t)p * f_d + (i - d)];
+            x[i] = t;
+        }
+    }
+}
+
 // The three blocks on fp32 MFMA, with the entries as the columns:
 // D_l [w_l x 16 entries] = W_l [w_l x K] R_{l-1}^T [K x 16 entries], one
 // 16-entry column tile at a time (four per wavefront of 64 entries).
@@ -575,6 +617,9 @@ __device__ __forceinline__ void wave_sync() {
 //   MODE 2: blocks 1 and 2; the sums of h_2 and h_2^2.
 //   MODE 3: all three blocks; the outputs go to LDS channel-major for the
 //           per-run max (see the file comment).
+//   MODE 5: all three blocks; the per-run argmax (the backward's routing).
+//   MODE 4: MODE 5, and the entry's record (h_0, h_1, h_2) for the backward
+//           of a batched lattice.
 // The normalisations are the per-cloud affines aff[cloud][..] (one row
 // when the lattice is unbatched or the caller gave the affines).  A chunk
 // whose entries all belong to one cloud (every chunk of an unbatched
@@ -594,7 +639,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_pointnet(const int32_t *__restric
                                                      unsigned int *__restrict__ keys, void *__restrict__ out,
                                                      float *__restrict__ rec, uint64_t *__restrict__ routed,
                                                      int32_t *__restrict__ win, uint2 *__restrict__ wslot) {
-    // MODE 3, 4: outputs [64 channels][64 entries], first the staged inputs;
+    // MODE 3..5: outputs [64 channels][64 entries], first the staged inputs;
     // MODE 1, 2: the staged inputs only
     constexpr int kYWave = MODE >= 3 ? kW3 * kYStride : 64 * (kMaxK0 + 1);
     __shared__ __attribute__((aligned(16))) float ysh[kWaves][kYWave];
@@ -730,7 +775,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_pointnet(const int32_t *__restric
     // cloud, the point's position and features and the vertex's mean (level
     // 2, which need level 1) one chunk ahead, so that a chunk's MFMAs never
     // wait on its own gathers.
-    const bool pos4 = d == 4 && ((reinterpret_cast<uintptr_t>(pos) | reinterpret_cast<uintptr_t>(mu)) & 15) == 0;
+    const bool pos4 = pos_rows16(pos, mu, d);
     struct Rows {
         int v, p;             // level 1
         int off, cnt, b;      // level 2
@@ -747,37 +792,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_pointnet(const int32_t *__restric
         R.off = valid ? vinfo[2 * R.v] : 0;
         R.cnt = valid ? vinfo[2 * R.v + 1] : 0;
         R.b = valid ? cloud_of(vkeys, batched, R.v) : -1;
-        if (pos4) {
-            // d = 4 with 16-byte aligned rows: the position and the mean as
-            // one 16-byte load each
-            const float4 pp = valid ? reinterpret_cast<const float4 *>(pos)[R.p] : make_float4(0.f, 0.f, 0.f, 0.f);
-            const float4 mm = valid ? reinterpret_cast<const float4 *>(mu)[R.v] : make_float4(0.f, 0.f, 0.f, 0.f);
-            R.x[0] = pp.x - mm.x;
-            R.x[1] = pp.y - mm.y;
-            R.x[2] = pp.z - mm.z;
-            R.x[3] = pp.w - mm.w;
-#pragma unroll
-            for (int i = 4; i < kMaxK0; ++i) R.x[i] = valid && i < k0 ? feat[(int64_t)R.p * f_d + (i - 4)] : 0.f;
-        } else if (d == 3) {
-            // d = 3: three adjacent 4-byte loads each (unconditional, so that
-            // they merge into one 12-byte load)
-            const int64_t p3 = (int64_t)(valid ? R.p : 0) * 3, v3 = (int64_t)(valid ? R.v : 0) * 3;
-            const float p0 = pos[p3], p1 = pos[p3 + 1], p2 = pos[p3 + 2];
-            const float m0 = mu[v3], m1 = mu[v3 + 1], m2 = mu[v3 + 2];
-            R.x[0] = valid ? p0 - m0 : 0.f;
-            R.x[1] = valid ? p1 - m1 : 0.f;
-            R.x[2] = valid ? p2 - m2 : 0.f;
-#pragma unroll
-            for (int i = 3; i < kMaxK0; ++i) R.x[i] = valid && i < k0 ? feat[(int64_t)R.p * f_d + (i - 3)] : 0.f;
-        } else {
-#pragma unroll
-            for (int i = 0; i < kMaxK0; ++i) {
-                float x = 0.f;
-                if (valid && i < d) x = pos[(int64_t)R.p * d + i] - mu[(int64_t)R.v * d + i];
-                else if (valid && i < k0) x = feat[(int64_t)R.p * f_d + (i - d)];
-                R.x[i] = x;
-            }
-        }
+        load_h0(valid, R.v, R.p, pos, mu, feat, d, f_d, pos4, R.x);
     };
     int64_t ch = c_first;
     Rows cur, nxt;
@@ -816,14 +831,15 @@ __global__ __launch_bounds__(kBlock, 2) void k_pointnet(const int32_t *__restric
             flush();
             if (uniform) sheld = bref;
         }
-        // MODE 4: the entry's record starts with h_0, and its routing mask
-        // is cleared (the backward's argmax sets the masks of the winners)
+        // MODE 4, 5: the entry's routing mask is cleared (the backward's
+        // argmax sets the masks of the winners); MODE 4: its record starts
+        // with h_0
+        if (MODE >= 4 && valid) routed[chunk0 + lane] = 0ull;
         if (MODE == 4 && valid) {
             float *R = rec + (chunk0 + lane) * kRec;
 #pragma unroll
             for (int i = 0; i < kMaxK0; i += 4)
                 *reinterpret_cast<float4 *>(R + i) = make_float4(cur.x[i], cur.x[i + 1], cur.x[i + 2], cur.x[i + 3]);
-            routed[chunk0 + lane] = 0ull;
         }
         // run flags: 1 first entry of a run, 2 last, 4 the run is the vertex's whole list
         int flags = 0, dest = -1;
@@ -976,7 +992,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_pointnet(const int32_t *__restric
                 }
             }
         }
-        if (MODE == 4) {
+        if (MODE >= 4) {
             wave_sync();
             // lane c: the first maximum of channel c over each run of the
             // wavefront's entries (the values the forward's max takes, in
@@ -1077,10 +1093,6 @@ constexpr int kPB3Base = 2 * kW2, kPB2Base = kW2 * kW1 + kW2 + 2 * kW1;
 constexpr int kPB3 = kPB3Base + kGnClouds * kW2 * 2;
 constexpr int kPB2 = kPB2Base + kGnClouds * kW1 * 2;
 constexpr int kPB1 = kW1 * kMaxK0 + kW1 + 2 * kMaxK0;
-__host__ __device__ inline int pb_len(int S, int batched) {
-    const int nc = batched ? kGnClouds : 1;
-    return S == 3 ? kPB3Base + nc * kW2 * 2 : (S == 2 ? kPB2Base + nc * kW1 * 2 : kPB1);
-}
 // staged floats per entry (64-entry chunks); an odd pitch puts a lane's own
 // row writes and the column reads on 64 different banks
 constexpr int kStg = 81;
@@ -1149,6 +1161,8 @@ __device__ __forceinline__ void load_params(const float *__restrict__ P, float *
     __syncthreads();
 }
 
+// REC: with the entries' records, dW3 is summed here too (lane c: row c).
+template <bool REC>
 __global__ __launch_bounds__(kBlock) void k_dpn_argmax(const int32_t *__restrict__ vinfo,
                                                        const uint64_t *__restrict__ vkeys, int batched,
                                                        const float *__restrict__ aff, const float *__restrict__ rec,
@@ -1161,19 +1175,35 @@ __global__ __launch_bounds__(kBlock) void k_dpn_argmax(const int32_t *__restrict
     const int64_t V = counters[CNT_V];
     const int64_t wave = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * kBlock) >> 6;
-    float dw[kW2], db = 0.f;
+    float dw[REC ? kW2 : 1], db = 0.f;
 #pragma unroll
-    for (int j = 0; j < kW2; ++j) dw[j] = 0.f;
+    for (int j = 0; j < (REC ? kW2 : 1); ++j) dw[j] = 0.f;
+    // the next vertex's list header, winners and gradient row are loaded a
+    // vertex ahead (its winners are used only if its list is in one chunk)
+    int64_t offn = 0;
+    int cntn = 0, wn = 0;
+    float gn = 0.f;
+    auto ahead = [&](int64_t v) {
+        if (v >= V) return;
+        offn = vinfo[2 * v];
+        cntn = vinfo[2 * v + 1];
+        wn = win[v * kW3 + lane];
+        gn = grad_out[v * kW3 + lane];
+    };
+    ahead(wave);
     for (int64_t v = wave; v < V; v += nwaves) {
-        const int64_t off = vinfo[2 * v];
-        const int cnt = vinfo[2 * v + 1];
+        const int64_t off = offn;
+        const int cnt = cntn;
+        const int mine = wn;
+        const float g = gn;
+        ahead(v + nwaves);
         // the winning entry of channel c (the first maximum in list order):
         // recorded by the records pass for a list within one chunk, else
         // the runs' slots combined in chunk order
         const int64_t j0 = off >> 6, j1 = (off + cnt - 1) >> 6;
         int be;
         if (j0 == j1) {
-            be = win[v * kW3 + lane];
+            be = mine;
         } else {
             float best = 0.f;
             be = (int)off;
@@ -1197,25 +1227,26 @@ __global__ __launch_bounds__(kBlock) void k_dpn_argmax(const int32_t *__restrict
             if (lane == leader) routed[w] = mk;
             todo &= ~mk;
         }
-        const float g = grad_out[v * kW3 + lane];
         db += g;
+        if (!REC) continue;
         const float *A = aff + (int64_t)cloud_of(vkeys, batched, (int)v) * kAffRow;
         const float *R = rec + (int64_t)be * kRec + kRecH2;
 #pragma unroll
-        for (int j = 0; j < kW2; ++j) dw[j] = fmaf(g, relu(fmaf(A[kAff2 + j], R[j], A[kAff2 + kW2 + j])), dw[j]);
+        for (int j = 0; j < (REC ? kW2 : 0); ++j)
+            dw[j] = fmaf(g, relu(fmaf(A[kAff2 + j], R[j], A[kAff2 + kW2 + j])), dw[j]);
     }
-    float *out = part + wave * kPArg;
+    float *out = part + wave * (REC ? kPArg : kW3);
 #pragma unroll
-    for (int j = 0; j < kW2; ++j) out[lane * kW2 + j] = dw[j];
-    out[kW3 * kW2 + lane] = db;
+    for (int j = 0; j < (REC ? kW2 : 0); ++j) out[lane * kW2 + j] = dw[j];
+    out[(REC ? kW3 * kW2 : 0) + lane] = db;
 }
 
-// One backward pass (see above).  din: the previous pass's stored per-entry
+// One backward pass over a batched lattice's records (see above).  din: the previous pass's stored per-entry
 // gradient (S = 2: dhn3 [E][32], S = 1: dhn2 [E][16]); dout: this pass's
 // (S = 3: dhn3, S = 2: dhn2).  One wavefront per workgroup.
-template <int S, bool BATCHED>
+template <int S>
 __global__ __launch_bounds__(64) void k_dpn_back(const int32_t *__restrict__ lvert,
-                                                 const uint64_t *__restrict__ vkeys, int batched, int use_gn, int G1,
+                                                 const uint64_t *__restrict__ vkeys, int G1,
                                                  int G2, const float *__restrict__ P, const float *__restrict__ aff,
                                                  const float *__restrict__ nrm, const float *__restrict__ gm,
                                                  const float *__restrict__ rec, const uint64_t *__restrict__ routed,
@@ -1240,19 +1271,9 @@ __global__ __launch_bounds__(64) void k_dpn_back(const int32_t *__restrict__ lve
     } else {
         for (int i = lane; i < kPadded; i += 64) Ps[i] = P[i];
     }
-    const bool tabbed = S != 1 && use_gn && BATCHED;
+    constexpr bool tabbed = S != 1;  // per-cloud group sums
     if (tabbed)
         for (int i = lane; i < kGnClouds * 2 * K; i += 64) tab[i] = 0.f;
-    // one cloud: its affines, normalisation and group means in LDS (the
-    // lanes read them as broadcasts instead of a global load per channel)
-    constexpr int kCst = kAffRow + kNrmRow + 2 * kW2 * 2;
-    __shared__ float cst[BATCHED ? 1 : kCst];
-    if (!BATCHED) {
-        for (int i = lane; i < kAffRow; i += 64) cst[i] = aff[i];
-        for (int i = lane; i < kNrmRow; i += 64) cst[kAffRow + i] = nrm[i];
-        if (S != 3)  // the group means exist from pass 2 on
-            for (int i = lane; i < 2 * kW2 * 2; i += 64) cst[kAffRow + kNrmRow + i] = gm[i];
-    }
     __syncthreads();
     const int64_t E = counters[CNT_E];
     const int G = S == 3 ? G2 : G1;
@@ -1267,10 +1288,10 @@ __global__ __launch_bounds__(64) void k_dpn_back(const int32_t *__restrict__ lve
         const int64_t e = e0 + lane;
         const bool live = e < E;
         const int v = live ? lvert[e] : 0;
-        const int cloud = BATCHED ? cloud_of(vkeys, 1, v) : 0;
-        const float *A = BATCHED ? aff + (int64_t)cloud * kAffRow : cst;
-        const float *N = BATCHED ? nrm + (int64_t)cloud * kNrmRow : cst + kAffRow;
-        const float *GM = BATCHED ? gm + (int64_t)cloud * 2 * kW2 * 2 : cst + kAffRow + kNrmRow;
+        const int cloud = cloud_of(vkeys, 1, v);
+        const float *A = aff + (int64_t)cloud * kAffRow;
+        const float *N = nrm + (int64_t)cloud * kNrmRow;
+        const float *GM = gm + (int64_t)cloud * 2 * kW2 * 2;
         const float *R = rec + (live ? e : 0) * kRec;
         // the part of the record this pass reads, as 16-byte loads (a lane's
         // record is 256 contiguous bytes)
@@ -1366,13 +1387,9 @@ __global__ __launch_bounds__(64) void k_dpn_back(const int32_t *__restrict__ lve
 #pragma unroll
             for (int j = 0; j < kW2; ++j) {
                 const float gj = Ps[kA2 + j] * dh[j];
-                if (use_gn) {
-                    const float xh = (rv[kRecH2 + j] - N[2 * 64 + 2 * j]) * N[2 * 64 + 2 * j + 1];
-                    const float *M = GM + kW2 * 2 + (j / gs3) * 2;
-                    dh[j] = live ? N[2 * 64 + 2 * j + 1] * (gj - M[0] - xh * M[1]) : 0.f;
-                } else {
-                    dh[j] = gj;
-                }
+                const float xh = (rv[kRecH2 + j] - N[2 * 64 + 2 * j]) * N[2 * 64 + 2 * j + 1];
+                const float *M = GM + kW2 * 2 + (j / gs3) * 2;
+                dh[j] = live ? N[2 * 64 + 2 * j + 1] * (gj - M[0] - xh * M[1]) : 0.f;
                 st[DH + j] = dh[j];
             }
             float dn[kW1];
@@ -1410,13 +1427,9 @@ __global__ __launch_bounds__(64) void k_dpn_back(const int32_t *__restrict__ lve
 #pragma unroll
             for (int c = 0; c < kW1; ++c) {
                 const float gc = Ps[kA1 + c] * dh[c];
-                if (use_gn) {
-                    const float xh = (rv[kRecH1 + c] - N[1 * 64 + 2 * c]) * N[1 * 64 + 2 * c + 1];
-                    const float *M = GM + (c / gs2) * 2;
-                    dh[c] = live ? N[1 * 64 + 2 * c + 1] * (gc - M[0] - xh * M[1]) : 0.f;
-                } else {
-                    dh[c] = gc;
-                }
+                const float xh = (rv[kRecH1 + c] - N[1 * 64 + 2 * c]) * N[1 * 64 + 2 * c + 1];
+                const float *M = GM + (c / gs2) * 2;
+                dh[c] = live ? N[1 * 64 + 2 * c + 1] * (gc - M[0] - xh * M[1]) : 0.f;
                 st[DH + c] = dh[c];
             }
 #pragma unroll
@@ -1468,7 +1481,7 @@ __global__ __launch_bounds__(64) void k_dpn_back(const int32_t *__restrict__ lve
     }
 
     // the wavefront's partial row
-    const int np = pb_len(S, batched);
+    constexpr int np = S == 3 ? kPB3 : (S == 2 ? kPB2 : kPB1);
     float *out = part + (int64_t)blockIdx.x * np;
     if (S == 3) {
         out[lane < kW2 ? kW2 + lane : lane - kW2] = vacc;  // dbeta3 (columns 0..31), dgamma3 (32..63)
@@ -1492,39 +1505,449 @@ __global__ __launch_bounds__(64) void k_dpn_back(const int32_t *__restrict__ lve
             if (i < NI && j < NJ) out[i * NJ + j] = macc[r];
         }
     }
-    if (S != 1 && use_gn) {
+    if (S != 1) {
         const int base = S == 3 ? kPB3Base : kPB2Base;
-        if (tabbed) {
-            __syncthreads();
-            for (int i = lane; i < kGnClouds * 2 * K; i += 64) out[base + i] = tab[i];
-        } else {
-            // one cloud: group sum = sum over the group's channels of gamma
-            // times the per-channel sum (dbeta's column, or dgamma's: dbeta
-            // in lane ch, dgamma in lane K + ch)
-            const int grp = lane >> 1, pt = lane & 1;
-            float x = 0.f;
-            for (int t = 0; t < gs; ++t) {
-                const int ch = (grp < G ? grp : 0) * gs + t;
-                const float y = __shfl(vacc, pt * K + ch);
-                x = fmaf(Ps[(S == 3 ? kA2P : kA1) + ch], y, x);
-            }
-            if (lane < 2 * K) out[base + lane] = grp < G ? x : 0.f;
-        }
-    } else if (S != 1) {
-        const int base = S == 3 ? kPB3Base : kPB2Base;
-        for (int i = lane; i < np - base; i += 64) out[base + i] = 0.f;
+        __syncthreads();
+        for (int i = lane; i < kGnClouds * 2 * K; i += 64) out[base + i] = tab[i];
     }
+}
+
+// One backward pass of an unbatched lattice (or of the fixed affine, which
+// has no per-cloud statistics), the entries as MFMA columns as in the
+// forward.  Nothing is kept from the forward: the positions, means and
+// features of an entry are 50 bytes that mostly hit in L2, and its h_1 and
+// h_2 cost 12 MFMAs per 16 entries, less than the 256-byte record of the
+// batched passes to write once and read three times.
+//   S = 3  the entries that win a channel (mask not 0; about 60% of a sweep's,
+//          the others' gradient is 0): queued per wavefront as the masks are
+//          read, 64 at a time.  dr2 = W3^T dh3 (dense: 128 MFMAs per 64
+//          entries), dhn3 stored; dgamma3, dbeta3, dW3.
+//   S = 2  every entry: dh2 from dhn3 and block 3's group means, dr1 = W2^T
+//          dh2, dhn2 stored; dW2, db2, dgamma2, dbeta2.
+//   S = 1  every entry: dh1 from dhn2, dr0 = W1^T dh1; dW1, db1, dgamma1,
+//          dbeta1.
+// Lane (q, j16) = (l / 16, l % 16) holds channel 4 q + r (+ 16 per row tile) of
+// entry j16 of each 16-entry tile in register r, which is at once the MFMA
+// output, the next product's B operand and 16 contiguous bytes of the
+// stored gradient.  Block 1's input is channel 4 r + q instead (the staged
+// operand order), and W1^T's rows are permuted to match.  A weight
+// gradient's K index is the entry: both factors of a tile go through LDS
+// (rows of 16 entries at a pitch of 20 floats: writes and 16-byte reads free
+// of bank conflicts), four entries per MFMA.  Per-channel sums stay in the
+// lanes until the end.  The workgroup's wavefronts are added in order and
+// its row is written; rowsum adds the rows: two calls give the same bits.
+// Four frames (2.1 M pairs, us), against the one-lane-per-entry passes over
+// records that a batched lattice still takes: winners 249 -> 182 (no record
+// written), argmax 240 -> 57 (dW3 moved into pass 3), passes 3 / 2 / 1
+// 340 / 318 / 229 -> 170 / 125 / 57.  What bounds them: pass 3 the matrix
+// cores (76 MFMAs of 16x16x4 per 16 winners, 78 us at full rate), passes 2
+// and 1 the gathers' latency at two and three wavefronts per SIMD.
+// Group means: from the previous pass's reduced sums (dgamma, dbeta of its
+// block), sum gn = sum over the group's channels of gamma dbeta, and of gamma
+// dgamma for gn xhat.
+constexpr int kQ3 = 2 * kW2 + kW3 * kW2, kQ2 = kPB2Base, kQ1 = kPB1;  // partial row lengths
+constexpr int kTP = 20;  // floats per staged channel of a 16-entry tile
+
+template <int S>
+__global__ __launch_bounds__(kBlock, 2) void k_dpn_pass(
+    const int32_t *__restrict__ list, const int32_t *__restrict__ lvert, const float *__restrict__ pos,
+    const float *__restrict__ feat, int d, int f_d, const float *__restrict__ P, const float *__restrict__ aff,
+    const float *__restrict__ nrm, const float *__restrict__ mu, const float *__restrict__ prev,
+    const double *__restrict__ rows, int use_gn, int G, const uint64_t *__restrict__ routed,
+    const float *__restrict__ grad_out, const float *__restrict__ din, float *__restrict__ dout,
+    const int32_t *__restrict__ counters, float *__restrict__ part) {
+    constexpr int NA = S == 3 ? kW3 : (S == 2 ? kW2 : kW1);    // dW rows (dh channels)
+    constexpr int NB = S == 3 ? kW2 : (S == 2 ? kW1 : kMaxK0); // dW columns (r channels)
+    constexpr int MA = NA / 16, MB = NB / 16;
+    constexpr int NP = S == 3 ? kQ3 : (S == 2 ? kQ2 : kQ1);
+    constexpr int XP = kMaxK0 + 1;
+    constexpr int kUnroll = S == 2 ? 4 : 1;                     // tiles of the entry loop
+    __shared__ float xs[kWaves][64 * XP];
+    __shared__ __attribute__((aligned(16))) float ts[kWaves][(NA + NB) * kTP];
+    __shared__ int queue[S == 3 ? kWaves : 1][S == 3 ? 128 : 1];
+    __shared__ float gms[S == 3 ? 1 : 2 * kW2];
+    __shared__ float red[NP];
+    // S = 3: W3^T's operands, [row tile][4 steps][lane] (in registers they
+    // would spill); S = 2, 1: registers
+    __shared__ f32x4_t wts[S == 3 ? 8 * 64 : 1];
+    // S = 3: block 3's affine a, s (bias folded in) and xhat's shift and scale,
+    // [which][row tile][lane quarter]
+    __shared__ f32x4_t cst[S == 3 ? 4 * 2 * 4 : 1];
+
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int q = lane >> 4, j16 = lane & 15;
+    float *X = xs[w], *Tl = ts[w];
+    const int64_t E = counters[CNT_E];
+
+    if (S == 3) {
+        for (int i = threadIdx.x; i < 8 * 64; i += kBlock) {
+            const int l = i & 63, t4 = (i >> 6) & 3, mt = i >> 8;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                wts[i][k] = P[kWt2 + (16 * t4 + 4 * (l >> 4) + k) * kW2 + 16 * mt + (l & 15)];
+        }
+        if (threadIdx.x < kW2) {
+            const int c = threadIdx.x;
+            const float a = aff[kAff2 + c], b = P[kB1 + c];
+            float *C = reinterpret_cast<float *>(cst);
+            C[c] = a;
+            C[kW2 + c] = fmaf(a, b, aff[kAff2 + kW2 + c]);
+            C[2 * kW2 + c] = b - nrm[2 * 64 + 2 * c];
+            C[3 * kW2 + c] = nrm[2 * 64 + 2 * c + 1];
+        }
+        __syncthreads();
+    }
+    if (S != 3) {
+        // the next block's group means per channel: sums over the cloud's rows
+        constexpr int KN = S == 2 ? kW2 : kW1;
+        const float *dgam = prev + (S == 2 ? 0 : kW2 * kW1 + kW2);
+        const float *dbet = dgam + KN;
+        if (threadIdx.x < KN) {
+            const int gs = KN / G, c0 = threadIdx.x / gs * gs;
+            double s0 = 0.0, s1 = 0.0;
+            for (int c = c0; c < c0 + gs; ++c) {
+                const double g = P[(S == 2 ? kA2 : kA1) + c];
+                s0 += g * dbet[c];
+                s1 += g * dgam[c];
+            }
+            const double n = use_gn ? rows[0] * gs : 0.0;
+            gms[2 * threadIdx.x] = n > 0.0 ? (float)(s0 / n) : 0.f;
+            gms[2 * threadIdx.x + 1] = n > 0.0 ? (float)(s1 / n) : 0.f;
+        }
+        __syncthreads();
+    }
+
+    // constants of this lane's channels
+    float wa1[4], a0[4], s0[4], a1[4], s1[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        wa1[t] = P[kWt0 + j16 * kMaxK0 + 4 * t + q];
+        a0[t] = aff[kAff0 + 4 * t + q];
+        s0[t] = aff[kAff0 + kMaxK0 + 4 * t + q];
+        a1[t] = aff[kAff1 + 4 * q + t];
+        s1[t] = fmaf(a1[t], P[kB0 + 4 * q + t], aff[kAff1 + kW1 + 4 * q + t]);
+    }
+    float wa2[2][4];
+    if (S != 1) {
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) wa2[mt][t] = P[kWt1 + (16 * mt + j16) * kW1 + 4 * q + t];
+    }
+    // normalised input xhat = (h + bias - mean) rstd of the block that is
+    // gone through (XB: bias - mean) and, S = 2, 1, of the block after it,
+    // with its rstd, gamma and group means (NB..)
+    constexpr int NX = S == 3 ? 8 : 4, NN = S == 2 ? 8 : (S == 1 ? 4 : 1);
+    float xb[S == 3 ? 1 : NX], xr[S == 3 ? 1 : NX], nb[NN], nr[NN], ng[NN], m0[NN], m1[NN];
+#pragma unroll
+    for (int i = 0; i < (S == 3 ? 0 : NX); ++i) {
+        const int c = S == 1 ? 4 * i + q : 4 * q + i;
+        const float *N = nrm + (S - 1) * 64 + 2 * c;
+        xb[i] = (S == 2 ? P[kB0 + c] : 0.f) - N[0];
+        xr[i] = N[1];
+    }
+    if (S != 3) {
+#pragma unroll
+        for (int i = 0; i < NN; ++i) {
+            const int c = 16 * (i / 4) + 4 * q + i % 4;
+            const float *N = nrm + S * 64 + 2 * c;
+            nb[i] = P[(S == 2 ? kB1 : kB0) + c] - N[0];
+            nr[i] = N[1];
+            ng[i] = P[(S == 2 ? kA2 : kA1) + c];
+            m0[i] = gms[2 * c];
+            m1[i] = gms[2 * c + 1];
+        }
+    }
+    // the transposed weights (A operands of dr = W^T dh)
+    constexpr int MT = S == 3 ? 2 : 1, NTK = NA / 4;
+    float wt[S == 3 ? 1 : NTK];
+    if (S != 3) {
+#pragma unroll
+        for (int t = 0; t < NTK; ++t) {
+            const int o = 16 * (t / 4) + 4 * q + t % 4;  // dh's channel
+            if (S == 2) wt[t] = P[kWt1 + o * kW1 + j16];
+            else wt[t] = P[kWt0 + o * kMaxK0 + 4 * (j16 & 3) + (j16 >> 2)];  // row 4 q + r: channel 4 r + q
+        }
+    }
+
+    f32x4_t acc[MA][MB];
+#pragma unroll
+    for (int i = 0; i < MA; ++i)
+#pragma unroll
+        for (int j = 0; j < MB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    float sb[NX], sg[NX], sdh[NN];  // dbeta, dgamma; db (S = 2, 1)
+#pragma unroll
+    for (int i = 0; i < NX; ++i) sb[i] = sg[i] = 0.f;
+#pragma unroll
+    for (int i = 0; i < NN; ++i) sdh[i] = 0.f;
+
+    const bool pos4 = pos_rows16(pos, mu, d);
+    const bool g16 = (reinterpret_cast<uintptr_t>(grad_out) & 15) == 0;
+    const int64_t nwaves = (int64_t)gridDim.x * kWaves;
+    const int64_t wave = (int64_t)blockIdx.x * kWaves + w;
+    const int64_t nch = (E + 63) / 64;
+    int64_t ch = wave;  // next chunk of masks (S = 3) or entries
+    int held = 0;       // queued winners (S = 3, wave-uniform)
+
+    // The next 64 entries: this lane's entry, or -1.  False when none is left.
+    auto next = [&](int &e) -> bool {
+        if (S != 3) {
+            if (ch >= nch) return false;
+            const int64_t k = ch * 64 + lane;
+            e = k < E ? (int)k : -1;
+            ch += nwaves;
+            return true;
+        }
+        int *Q = queue[S == 3 ? w : 0];
+        while (held < 64 && ch < nch) {
+            const int64_t k = ch * 64 + lane;
+            const bool on = k < E && routed[k] != 0ull;
+            const unsigned long long b = __ballot(on);
+            if (on) Q[held + __popcll(b & ((1ull << lane) - 1ull))] = (int)k;
+            held += __popcll(b);
+            ch += nwaves;
+        }
+        if (held == 0) return false;
+        wave_sync();
+        const int n = held < 64 ? held : 64;
+        e = lane < n ? Q[lane] : -1;
+        const int rest = lane + 64 < held ? Q[64 + lane] : -1;
+        wave_sync();
+        held -= n;
+        if (lane < held) Q[lane] = rest;
+        wave_sync();
+        return true;
+    };
+
+    // software pipeline: the entries' vertex, point and mask are loaded two
+    // rounds ahead, their h_0 one round ahead, and the incoming gradient of a
+    // 16-entry tile one tile ahead
+    struct Entry {
+        int e, v, p, lo, hi;
+    };
+    auto locate = [&](Entry &x) {
+        x.v = x.e >= 0 ? lvert[x.e] : 0;
+        x.p = x.e >= 0 ? list_point(list[2 * (int64_t)x.e]) : 0;
+        const uint64_t mk = S != 1 && x.e >= 0 ? routed[x.e] : 0ull;
+        x.lo = (int)(uint32_t)mk;
+        x.hi = (int)(mk >> 32);
+    };
+    constexpr int NG = NA / 16;  // 16-byte loads per lane and tile
+    auto load_in = [&](const Entry &x, int nt, float4 *t4) {
+        const int src = 16 * nt + j16;
+        if (S == 3) {
+            const float *g = grad_out + (int64_t)__shfl(x.v, src) * kW3 + 4 * q;  // row 0 where there is no entry
+#pragma unroll
+            for (int mt = 0; mt < NG; ++mt)
+                t4[mt] = g16 ? *reinterpret_cast<const float4 *>(g + 16 * mt)
+                             : make_float4(g[16 * mt], g[16 * mt + 1], g[16 * mt + 2], g[16 * mt + 3]);
+        } else {
+            const int en = __shfl(x.e, src);
+            const bool has = en >= 0 && (S == 1 || (__shfl(x.lo, src) | __shfl(x.hi, src)) != 0);
+#pragma unroll
+            for (int mt = 0; mt < NG; ++mt)
+                t4[mt] = has ? *reinterpret_cast<const float4 *>(din + (int64_t)en * NA + 16 * mt + 4 * q)
+                             : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    Entry cur, nxt;
+    cur.e = nxt.e = -1;
+    bool more = next(cur.e);
+    bool more2 = false;
+    float x[kMaxK0];
+    float4 in4[NG], in4n[NG];
+    if (more) {
+        locate(cur);
+        load_h0(cur.e >= 0, cur.v, cur.p, pos, mu, feat, d, f_d, pos4, x);
+        more2 = next(nxt.e);
+        if (!more2) nxt.e = -1;
+        locate(nxt);
+        load_in(cur, 0, in4);
+    }
+    while (more) {
+#pragma unroll
+        for (int i = 0; i < kMaxK0; ++i) X[lane * XP + i] = x[i];
+        wave_sync();
+        load_h0(nxt.e >= 0, nxt.v, nxt.p, pos, mu, feat, d, f_d, pos4, x);
+        Entry far;
+        far.e = -1;
+        const bool more3 = more2 && next(far.e);
+        if (!more3) far.e = -1;
+        locate(far);
+        // S = 3, 1: one tile at a time (unrolled, S = 3 spills 94 registers:
+        // 350 against 172 us on the four frames, S = 1 71 against 66); S = 2
+        // fits, and gains from the overlap of its tiles (148 against 127)
+#pragma unroll kUnroll
+        for (int nt = 0; nt < 4; ++nt) {
+            const int src = 16 * nt + j16;
+            const int en = __shfl(cur.e, src);
+            const bool live = en >= 0;
+            load_in(nt < 3 ? cur : nxt, (nt + 1) & 3, in4n);
+            // this pass's incoming gradient: dh3 (S = 3: g on the channels
+            // won), dhn of the block after (S = 2, 1)
+            float dh[NA / 4];
+            const uint32_t lo = S == 3 ? (uint32_t)__shfl(cur.lo, src) : 0u;
+            const uint32_t hi = S == 3 ? (uint32_t)__shfl(cur.hi, src) : 0u;
+#pragma unroll
+            for (int mt = 0; mt < NG; ++mt) {
+                const float4 t4 = in4[mt];
+                const uint32_t m = S == 3 ? (mt < 2 ? lo : hi) >> (16 * (mt & 1) + 4 * q) : 15u;
+                dh[4 * mt + 0] = (m & 1u) ? t4.x : 0.f;
+                dh[4 * mt + 1] = (m & 2u) ? t4.y : 0.f;
+                dh[4 * mt + 2] = (m & 4u) ? t4.z : 0.f;
+                dh[4 * mt + 3] = (m & 8u) ? t4.w : 0.f;
+            }
+            // the forward up to this block, with its own arithmetic
+            float h0[4], hn0[4];
+            f32x4_t d1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                h0[t] = X[src * XP + 4 * t + q];
+                hn0[t] = fmaf(a0[t], h0[t], s0[t]);
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) d1 = mfma16(wa1[t], relu(hn0[t]), d1);
+            float hn1[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) hn1[t] = fmaf(a1[t], d1[t], s1[t]);
+            f32x4_t d2[2];
+            if (S != 1) {
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt) {
+                    d2[mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) d2[mt] = mfma16(wa2[mt][t], relu(hn1[t]), d2[mt]);
+                }
+            }
+            // the group normalisation of the block after (or its affine)
+            if (S != 3) {
+#pragma unroll
+                for (int i = 0; i < NN; ++i) {
+                    const float g = ng[i] * dh[i];
+                    if (use_gn) {
+                        const float xh = ((S == 2 ? d2[i / 4][i % 4] : d1[i % 4]) + nb[i]) * nr[i];
+                        dh[i] = live ? nr[i] * (g - m0[i] - xh * m1[i]) : 0.f;
+                    } else {
+                        dh[i] = g;
+                    }
+                    sdh[i] += dh[i];
+                }
+            }
+            // dr = W^T dh, through the ReLU and into the sums
+            f32x4_t dr[MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                dr[mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int t4 = 0; t4 < NTK / 4; ++t4) {
+                    f32x4_t a;
+                    if (S == 3) a = wts[(4 * mt + t4) * 64 + lane];
+                    else a = f32x4_t{wt[S == 3 ? 0 : 4 * t4], wt[S == 3 ? 0 : 4 * t4 + 1], wt[S == 3 ? 0 : 4 * t4 + 2],
+                                     wt[S == 3 ? 0 : 4 * t4 + 3]};
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) dr[mt] = mfma16(a[k], dh[4 * t4 + k], dr[mt]);
+                }
+            }
+            f32x4_t ca, cs, cb, cr;  // S = 3: this row tile's constants
+#pragma unroll
+            for (int i = 0; i < NX; ++i) {
+                if (S == 3 && i % 4 == 0) {
+                    ca = cst[i + q];
+                    cs = cst[8 + i + q];
+                    cb = cst[16 + i + q];
+                    cr = cst[24 + i + q];
+                }
+                const float h = S == 3 ? d2[i / 4][i % 4] : (S == 2 ? d1[i % 4] : h0[i % 4]);
+                const float hn = S == 3 ? fmaf(ca[i % 4], h, cs[i % 4]) : (S == 2 ? hn1[i % 4] : hn0[i % 4]);
+                const float xh = S == 3 ? (h + cb[i % 4]) * cr[i % 4] : (h + xb[S == 3 ? 0 : i]) * xr[S == 3 ? 0 : i];
+                const float dn = live && hn > 0.f ? dr[i / 4][i % 4] : 0.f;
+                dr[i / 4][i % 4] = dn;
+                sb[i] += dn;
+                sg[i] = fmaf(dn, xh, sg[i]);
+                Tl[(NA + (S == 1 ? 4 * i + q : 16 * (i / 4) + 4 * q + i % 4)) * kTP + j16] = relu(hn);
+            }
+            if (S != 1 && live) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    *reinterpret_cast<f32x4_t *>(dout + (int64_t)en * NB + 16 * mt + 4 * q) = dr[mt];
+            }
+#pragma unroll
+            for (int i = 0; i < NA / 4; ++i) Tl[(16 * (i / 4) + 4 * q + i % 4) * kTP + j16] = dh[i];
+            wave_sync();
+            // dW += dh r^T over the tile's 16 entries
+            f32x4_t fb[MB];
+#pragma unroll
+            for (int j = 0; j < MB; ++j) fb[j] = *reinterpret_cast<const f32x4_t *>(Tl + (NA + 16 * j + j16) * kTP + 4 * q);
+#pragma unroll
+            for (int i = 0; i < MA; ++i) {
+                const f32x4_t fa = *reinterpret_cast<const f32x4_t *>(Tl + (16 * i + j16) * kTP + 4 * q);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int j = 0; j < MB; ++j) acc[i][j] = mfma16(fa[k], fb[j][k], acc[i][j]);
+            }
+            wave_sync();
+#pragma unroll
+            for (int mt = 0; mt < NG; ++mt) in4[mt] = in4n[mt];
+        }
+        cur = nxt;
+        nxt = far;
+        more = more2;
+        more2 = more3;
+    }
+
+    // the workgroup's partial row: its wavefronts' sums added in order
+    auto quarter = [&](float y) {
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) y += __shfl_xor(y, o);
+        return y;
+    };
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        sb[i] = quarter(sb[i]);
+        sg[i] = quarter(sg[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < NN; ++i) sdh[i] = quarter(sdh[i]);
+    constexpr int DW = S == 3 ? 2 * kW2 : 0;                 // offsets in the row: dW,
+    constexpr int GA = S == 3 ? 0 : NA * NB + NA;            // dgamma,
+    constexpr int KX = S == 3 ? kW2 : (S == 2 ? kW1 : kMaxK0);  // then dbeta [KX]; db at NA NB (S = 2, 1)
+    for (int u = 0; u < kWaves; ++u) {
+        if (w == u) {
+            auto add = [&](int at, float y) { red[at] = u == 0 ? y : red[at] + y; };
+#pragma unroll
+            for (int i = 0; i < MA; ++i)
+#pragma unroll
+                for (int j = 0; j < MB; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) add(DW + (16 * i + 4 * q + r) * NB + 16 * j + j16, acc[i][j][r]);
+            if (j16 == 0) {
+#pragma unroll
+                for (int i = 0; i < NX; ++i) {
+                    const int c = S == 1 ? 4 * i + q : 16 * (i / 4) + 4 * q + i % 4;
+                    add(GA + c, sg[i]);
+                    add(GA + KX + c, sb[i]);
+                }
+                if (S != 3) {
+#pragma unroll
+                    for (int i = 0; i < NN; ++i) add(NA * NB + 16 * (i / 4) + 4 * q + i % 4, sdh[i]);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    for (int i = threadIdx.x; i < NP; i += kBlock) part[(int64_t)blockIdx.x * NP + i] = red[i];
 }
 
 // The group means of block l's (l = 1: block 2, l = 2: block 3) gradient
 // sums: gm[cloud][l - 1][group] = (sum gn, sum gn xhat) / (rows * group size).
 __global__ __launch_bounds__(kBlock) void k_dpn_gnmean(const float *__restrict__ sums, int l, int G,
                                                        const double *__restrict__ rows,
-                                                       const int32_t *__restrict__ counters, int batched,
+                                                       const int32_t *__restrict__ counters,
                                                        float *__restrict__ gm) {
     const int K = l == 2 ? kW2 : kW1;
     const int gsz = K / G;
-    const int nc = num_clouds(counters, batched);  // the clouds k_dpn_norm counted
+    const int nc = num_clouds(counters, 1);  // the clouds k_dpn_norm counted
     for (int i = threadIdx.x + blockIdx.x * kBlock; i < nc * G; i += gridDim.x * kBlock) {
         const int b = i / G, gi = i % G;
         const double n = rows[b] * gsz;
@@ -1538,8 +1961,8 @@ __global__ __launch_bounds__(kBlock) void k_dpn_gnmean(const float *__restrict__
 // The reduced sums in the caller's layout: per block, d(gamma or a) [K],
 // d(beta or s) [K], dW [w][K], db [w].
 __global__ __launch_bounds__(kBlock) void k_dpn_out(const float *__restrict__ r1, const float *__restrict__ r2,
-                                                    const float *__restrict__ r3, const float *__restrict__ rarg,
-                                                    int k0, float *__restrict__ grad) {
+                                                    const float *__restrict__ r3, const float *__restrict__ dw3,
+                                                    const float *__restrict__ db3, int k0, float *__restrict__ grad) {
     const int n1 = 2 * k0 + kW1 * k0 + kW1, n2 = 2 * kW1 + kW2 * kW1 + kW2, n3 = 2 * kW2 + kW3 * kW2 + kW3;
     for (int i = threadIdx.x + blockIdx.x * kBlock; i < n1 + n2 + n3; i += gridDim.x * kBlock) {
         float x;
@@ -1560,8 +1983,8 @@ __global__ __launch_bounds__(kBlock) void k_dpn_out(const float *__restrict__ r1
         } else {
             const int j = i - n1 - n2;
             if (j < 2 * kW2) x = r3[j];                              // dgamma3, dbeta3
-            else if (j < 2 * kW2 + kW3 * kW2) x = rarg[j - 2 * kW2]; // dW3
-            else x = rarg[kW3 * kW2 + (j - 2 * kW2 - kW3 * kW2)];    // db3
+            else if (j < 2 * kW2 + kW3 * kW2) x = dw3[j - 2 * kW2];  // dW3
+            else x = db3[j - 2 * kW2 - kW3 * kW2];                  // db3
         }
         grad[i] = x;
     }
@@ -1674,14 +2097,16 @@ hipError_t launch_distribute_pointnet(lattice *L, const float *pos, const float 
 // Scratch of the backward (offsets in bytes, 256-aligned).
 struct DpnLayout {
     int64_t rec, routed, win, wslot, d3, d2, nrm, rows, gm, parg, pb3, pb2, pb1, r3, r2, r1, rarg, tmp, total;
-    int nwaves_arg, nwaves;
+    int nwaves_arg, nwaves_route, nwaves, nblk;
 };
 
 static DpnLayout dpn_layout(const lattice *L) {
     auto al = [](int64_t x) { return (x + 255) / 256 * 256; };
     DpnLayout l;
     l.nwaves_arg = L->cu_count * 4 * kWaves;  // four workgroups of four wavefronts per CU
-    l.nwaves = L->cu_count * 4;               // backward passes: four one-wavefront workgroups per CU
+    l.nwaves_route = L->cu_count * 8 * kWaves;  // without dW3's registers, eight
+    l.nwaves = L->cu_count * 4;               // batched passes: four one-wavefront workgroups per CU
+    l.nblk = L->cu_count * 2;                 // the other passes' workgroups: two per CU stay resident
     const int64_t V = L->max_vertices, E = (int64_t)(L->d + 1) * L->max_points;
     int64_t at = 0;
     l.rec = at;    at += al(E * kRec * 4);
@@ -1733,50 +2158,73 @@ hipError_t launch_distribute_backward(lattice *L, const float *pos, const float 
     hipLaunchKernelGGL(k_dpn_norm, dim3((unsigned)((kGnClouds * 96 + kWaves - 1) / kWaves)), dim3(kBlock), 0,
                        L->stream, L->pn_stats, L->counters, batched, use_gn, k0, G0, G1, G2, eps, F(l.nrm), rows);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    // the per-entry records (h_0 .. h_3) by the forward's own MFMA pass, so
-    // that the argmax sees exactly the values the forward's max took
     uint64_t *routed = reinterpret_cast<uint64_t *>(s + l.routed);
+    int32_t *win = reinterpret_cast<int32_t *>(s + l.win);
+    uint2 *wslot = reinterpret_cast<uint2 *>(s + l.wslot);
     const unsigned g_p = grid_for((int64_t)(L->d + 1) * L->m, kBlock, L->cu_count, 2);
-    hipLaunchKernelGGL((k_pointnet<4, false>), dim3(g_p), dim3(kBlock), 0, L->stream, L->list, L->lvert, L->vinfo,
-                       L->vkeys, batched, pos, feat, L->d, f_d, L->pn_params, L->pn_aff, L->mu, L->counters,
-                       L->pn_stats, L->pn_keys, nullptr, F(l.rec), routed, reinterpret_cast<int32_t *>(s + l.win),
-                       reinterpret_cast<uint2 *>(s + l.wslot));
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_dpn_argmax, dim3((unsigned)(l.nwaves_arg / kWaves)), dim3(kBlock), 0, L->stream, L->vinfo,
-                       L->vkeys, batched, L->pn_aff, F(l.rec), reinterpret_cast<const int32_t *>(s + l.win),
-                       reinterpret_cast<const uint2 *>(s + l.wslot), grad_out, L->counters, routed, F(l.parg));
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const int nwaves_a = batched ? l.nwaves_arg : l.nwaves_route;
+    // the winners (and a batched lattice's records) by the forward's own MFMA
+    // pass, so that the argmax sees exactly the values the forward's max took
+    auto winners = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(g_p), dim3(kBlock), 0, L->stream, L->list, L->lvert, L->vinfo, L->vkeys, batched,
+                           pos, feat, L->d, f_d, L->pn_params, L->pn_aff, L->mu, L->counters, L->pn_stats, L->pn_keys,
+                           nullptr, F(l.rec), routed, win, wslot);
+        return hipGetLastError();
+    };
+    auto route = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)(nwaves_a / kWaves)), dim3(kBlock), 0, L->stream, L->vinfo, L->vkeys, batched, L->pn_aff,
+                           F(l.rec), win, wslot, grad_out, L->counters, routed, F(l.parg));
+        return hipGetLastError();
+    };
     auto reduce = [&](const float *part, int64_t nrows, int64_t n, float *out) {
         return rowsum::sum(L->stream, part, nrows, n, F(l.tmp), out);
     };
+    auto out = [&](const float *dw3, const float *db3) {
+        hipLaunchKernelGGL(k_dpn_out, dim3(16), dim3(kBlock), 0, L->stream, F(l.r1), F(l.r2), F(l.r3), dw3, db3, k0,
+                           grad_params);
+        return hipGetLastError();
+    };
+    if (!batched) {
+        auto pass = [&](auto kern, const float *prev, int G, const float *din, float *dout, int64_t part_off,
+                        int nblk) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(kBlock), 0, L->stream, L->list, L->lvert, pos, feat,
+                               L->d, f_d, L->pn_params, L->pn_aff, F(l.nrm), L->mu, prev, rows, use_gn, G, routed,
+                               grad_out, din, dout, L->counters, F(part_off));
+            return hipGetLastError();
+        };
+        const int nblk1 = L->cu_count * 3;  // pass 1's registers let a CU hold three
+        if ((e = winners(k_pointnet<5, false>)) != hipSuccess) return e;
+        if ((e = route(k_dpn_argmax<false>)) != hipSuccess) return e;
+        if ((e = pass(k_dpn_pass<3>, nullptr, G2, nullptr, F(l.d3), l.pb3, l.nblk)) != hipSuccess) return e;
+        if ((e = reduce(F(l.pb3), l.nblk, kQ3, F(l.r3))) != hipSuccess) return e;
+        if ((e = pass(k_dpn_pass<2>, F(l.r3), G2, F(l.d3), F(l.d2), l.pb2, l.nblk)) != hipSuccess) return e;
+        if ((e = reduce(F(l.pb2), l.nblk, kQ2, F(l.r2))) != hipSuccess) return e;
+        if ((e = pass(k_dpn_pass<1>, F(l.r2), G1, F(l.d2), nullptr, l.pb1, nblk1)) != hipSuccess) return e;
+        const rowsum::Job last[2] = {{F(l.pb1), F(l.r1), nblk1, kQ1}, {F(l.parg), F(l.rarg), nwaves_a, kW3}};
+        if ((e = rowsum::sum_all(L->stream, last, 2, F(l.tmp))) != hipSuccess) return e;
+        return out(F(l.r3) + 2 * kW2, F(l.rarg));
+    }
     auto back = [&](auto kern, int K, const float *din, float *dout, int64_t part_off) {
-        const size_t tab = (use_gn && batched && K > 0) ? (size_t)kGnClouds * 2 * K * sizeof(float) : 0;
-        hipLaunchKernelGGL(kern, dim3((unsigned)l.nwaves), dim3(64), tab, L->stream, L->lvert, L->vkeys, batched,
-                           use_gn, G1, G2, L->pn_params, L->pn_aff, F(l.nrm), F(l.gm), F(l.rec), routed, grad_out,
-                           din, dout, L->counters, F(part_off));
+        const size_t tab = (size_t)kGnClouds * 2 * K * sizeof(float);
+        hipLaunchKernelGGL(kern, dim3((unsigned)l.nwaves), dim3(64), tab, L->stream, L->lvert, L->vkeys, G1, G2,
+                           L->pn_params, L->pn_aff, F(l.nrm), F(l.gm), F(l.rec), routed, grad_out, din, dout,
+                           L->counters, F(part_off));
         return hipGetLastError();
     };
     auto gnmean = [&](const float *sums, int lb, int G) {
-        hipLaunchKernelGGL(k_dpn_gnmean, dim3(1), dim3(kBlock), 0, L->stream, sums, lb, G, rows, L->counters, batched,
-                           F(l.gm));
+        hipLaunchKernelGGL(k_dpn_gnmean, dim3(1), dim3(kBlock), 0, L->stream, sums, lb, G, rows, L->counters, F(l.gm));
         return hipGetLastError();
     };
-    if ((e = batched ? back(k_dpn_back<3, true>, kW2, nullptr, F(l.d3), l.pb3)
-                   : back(k_dpn_back<3, false>, kW2, nullptr, F(l.d3), l.pb3)) != hipSuccess)
-        return e;
-    if ((e = reduce(F(l.pb3), l.nwaves, pb_len(3, batched), F(l.r3))) != hipSuccess) return e;
-    if (use_gn && (e = gnmean(F(l.r3) + kPB3Base, 2, G2)) != hipSuccess) return e;
-    if ((e = batched ? back(k_dpn_back<2, true>, kW1, F(l.d3), F(l.d2), l.pb2)
-                   : back(k_dpn_back<2, false>, kW1, F(l.d3), F(l.d2), l.pb2)) != hipSuccess)
-        return e;
-    if ((e = reduce(F(l.pb2), l.nwaves, pb_len(2, batched), F(l.r2))) != hipSuccess) return e;
-    if (use_gn && (e = gnmean(F(l.r2) + kPB2Base, 1, G1)) != hipSuccess) return e;
-    if ((e = batched ? back(k_dpn_back<1, true>, 0, F(l.d2), nullptr, l.pb1)
-                   : back(k_dpn_back<1, false>, 0, F(l.d2), nullptr, l.pb1)) != hipSuccess)
-        return e;
+    if ((e = winners(k_pointnet<4, false>)) != hipSuccess) return e;
+    if ((e = route(k_dpn_argmax<true>)) != hipSuccess) return e;
+    if ((e = back(k_dpn_back<3>, kW2, nullptr, F(l.d3), l.pb3)) != hipSuccess) return e;
+    if ((e = reduce(F(l.pb3), l.nwaves, kPB3, F(l.r3))) != hipSuccess) return e;
+    if ((e = gnmean(F(l.r3) + kPB3Base, 2, G2)) != hipSuccess) return e;
+    if ((e = back(k_dpn_back<2>, kW1, F(l.d3), F(l.d2), l.pb2)) != hipSuccess) return e;
+    if ((e = reduce(F(l.pb2), l.nwaves, kPB2, F(l.r2))) != hipSuccess) return e;
+    if ((e = gnmean(F(l.r2) + kPB2Base, 1, G1)) != hipSuccess) return e;
+    if ((e = back(k_dpn_back<1>, 0, F(l.d2), nullptr, l.pb1)) != hipSuccess) return e;
     const rowsum::Job last[2] = {{F(l.pb1), F(l.r1), l.nwaves, kPB1}, {F(l.parg), F(l.rarg), l.nwaves_arg, kPArg}};
     if ((e = rowsum::sum_all(L->stream, last, 2, F(l.tmp))) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_dpn_out, dim3(16), dim3(kBlock), 0, L->stream, F(l.r1), F(l.r2), F(l.r3), F(l.rarg), k0,
-                       grad_params);
-    return hipGetLastError();
+    return out(F(l.rarg), F(l.rarg) + kW3 * kW2);
 }

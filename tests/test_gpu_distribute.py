@@ -489,3 +489,50 @@ def test_distribute_pointnet_backward_repeatable_and_checks():
                                                   ctypes.c_float(1e-5), ctypes.c_void_p(G.data_ptr()),
                                                   ctypes.c_void_p(out.data_ptr()))
     assert st != 0
+
+
+@pytest.mark.parametrize("d,m,sigma,f_d,groups", [
+    (1, 21, 0.05, 2, "default"), (2, 13, 0.5, 0, "default"), (3, 5, 10.0, 3, (3, 4, 8)),
+    (3, 700, 0.2, 6, "default"), (3, 4099, 1.0, 13, (4, 2, 1)), (2, 20000, 0.05, 3, (5, 16, 4)),
+    (3, 30000, 3.0, 1, "default")])
+def test_distribute_pointnet_backward_one_cloud_both_paths(d, m, sigma, f_d, groups):
+    """The passes of an unbatched lattice against those of a batched one
+    (another set of kernels) on the same cloud, all batch ids 0: fewer pairs
+    than one wavefront's 64, a last chunk partly empty, lists of a few and of
+    thousands of pairs (few winners among them), grad_out rows off a 16-byte
+    boundary.  The two differ by rounding and by which side of a near tie or
+    of a ReLU's zero a row falls on (their statistics' sums are ordered
+    differently): each such row moves a gradient by about one row's share,
+    1 / sqrt(pairs) of its norm at worst; 1e-2 allows a few, and a misplaced
+    row, channel or group mean is far outside.  (A single point is left out:
+    its channels have variance 0, and each block's 1 / sqrt(eps) = 316 turns
+    rounding into gradients.)  Two calls give the same bits."""
+    from paper_2108_03917_amd import Lattice
+
+    w = random_cloud(m, d, seed=640 + d, extent=1.0, C=max(f_d, 1))
+    pos = to_dev(w.pos)
+    feat = to_dev(w.feat[:, :f_d]) if f_d else None
+    k0 = d + f_d
+    params = Lattice.pack_pointnet(pointnet_gn_weights(k0, seed=641)).to("cuda:0")
+    L = Lattice(d, sigma, max_points=m)
+    gp = torch.randn(m, 64, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(642))
+    out = []
+    for batch in (None, torch.zeros(m, dtype=torch.int32, device="cuda:0")):
+        L.splat(pos, None, batch)
+        rows = L.slice_backward(gp)          # the same gradient rows in either vertex order
+        flat = torch.empty(rows.numel() + 1, device="cuda:0")
+        G = flat[1:].view(rows.shape) if batch is None else rows
+        G.copy_(rows)
+        a = L.distribute_pointnet_backward(pos, feat, params, G, groups=groups)
+        assert torch.equal(a, L.distribute_pointnet_backward(pos, feat, params, G, groups=groups))
+        out.append(a.double())
+    k, at = (k0, 16, 32), 0
+    for li, wd in enumerate((16, 32, 64)):
+        for n in (k[li], k[li], wd * k[li], wd):
+            x, y = out[0][at:at + n], out[1][at:at + n]
+            at += n
+            assert torch.isfinite(x).all()
+            # rounding noise alone where a gradient cancels to zero
+            floor = 1e-5 * max(out[1].norm().item(), 1e-3)
+            assert (x - y).norm() <= 1e-2 * y.norm() + floor, (li, n, (x - y).norm().item(), y.norm().item())
+    L.close()
