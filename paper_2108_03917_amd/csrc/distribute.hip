@@ -626,7 +626,7 @@ __device__ __forceinline__ void load_h0(bool valid, int v, int p, const float *_
 // lattice) uses that cloud's affines, kept in registers while the cloud
 // stays the same; a chunk that spans clouds loads each entry's own.
 template <int MODE, bool OUT_BF16>
-__global__ __launch_bounds__(kBlock, 2) void k_pointnet(const int32_t *__restrict__ list,
+__global__ __launch_bounds__(kBlock, MODE == 1 ? 4 : (MODE == 2 ? 3 : 2)) void k_pointnet(const int32_t *__restrict__ list,
                                                      const int32_t *__restrict__ lvert,
                                                      const int32_t *__restrict__ vinfo,
                                                      const uint64_t *__restrict__ vkeys, int batched,
@@ -2073,12 +2073,22 @@ hipError_t launch_distribute_pointnet(lattice *L, const float *pos, const float 
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if ((e = finalize(0)) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_pointnet<1, false>), dim3(g_p), dim3(kBlock), 0, L->stream, L->list, L->lvert, L->vinfo,
+        // the statistics passes hold less: up to four and three workgroups
+        // per CU (four frames 47 -> 41 and 76 -> 66 us against two), as long as
+        // a wavefront has eight chunks to one hand-over of its sums (the
+        // indoor room's 580 000 pairs: 22.7 us with two, 23.9 with four)
+        auto stat_grid = [&](int most) {
+            int64_t per_cu = E / (64 * 8 * kWaves) / L->cu_count;
+            per_cu = per_cu < 2 ? 2 : (per_cu > most ? most : per_cu);
+            return grid_for(E, kBlock, L->cu_count, (int)per_cu);
+        };
+        const unsigned g_p1 = stat_grid(4), g_p2 = stat_grid(3);
+        hipLaunchKernelGGL((k_pointnet<1, false>), dim3(g_p1), dim3(kBlock), 0, L->stream, L->list, L->lvert, L->vinfo,
                            L->vkeys, batched, pos, feat, d, f_d, L->pn_params, L->pn_aff, mu, L->counters,
                            L->pn_stats, L->pn_keys, out, nullptr, nullptr, nullptr, nullptr);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if ((e = finalize(1)) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_pointnet<2, false>), dim3(g_p), dim3(kBlock), 0, L->stream, L->list, L->lvert, L->vinfo,
+        hipLaunchKernelGGL((k_pointnet<2, false>), dim3(g_p2), dim3(kBlock), 0, L->stream, L->list, L->lvert, L->vinfo,
                            L->vkeys, batched, pos, feat, d, f_d, L->pn_params, L->pn_aff, mu, L->counters,
                            L->pn_stats, L->pn_keys, out, nullptr, nullptr, nullptr, nullptr);
         if ((e = hipGetLastError()) != hipSuccess) return e;
