@@ -790,3 +790,38 @@ def test_conv_segment_shapes(C_in, C_out, in_dtype, dtype, d, m):
         tol = REL_F32 * scale + (BF16_ULP * np.abs(ref) if out_dtype == "bf16" else 0.0)
         assert_close_scaled(got, ref, tol, 1.0, f"{in_dtype} rows {dtype} conv {C_in}x{C_out} d={d} out {out_dtype}")
     L.close()
+
+
+@pytest.mark.parametrize("C_in,C_out,m", [(64, 64, 9000), (36, 100, 9000), (96, 96, 120000)])
+def test_conv_f32_extreme_values(C_in, C_out, m):
+    """fp32 rows with infinities, NaN and values beyond bf16's largest among
+    ordinary ones: infinite and NaN outputs where a sum of the same products
+    has them, the others within the usual 1e-5 of their sum of |terms|
+    (values of 3.39e38 times weights of 0.1 stay finite); rows of about
+    1e-28 keep the same relative accuracy."""
+    w = random_cloud(m, 3, seed=1300, extent=1.0, C=1)
+    L = _lattice(3, 0.25, w.m)
+    g = GpuLattice(L, w.pos, w.feat)
+    lat = O.build(w.pos, 0.25)
+    nbr = O.neighbors(lat)
+    x = random_rows(lat.V, C_in, seed=1301)
+    rng = np.random.default_rng(1302)
+    rows = rng.choice(lat.V, size=24, replace=False)
+    for i, v in enumerate(rows):
+        x[v, rng.integers(C_in)] = (np.inf, -np.inf, np.nan, 3.39e38, -3.39e38, 1e-40)[i % 6]
+    W = (0.1 * np.sign(rng.standard_normal((C_out, 9, C_in)))).astype(np.float32)
+    W[:, :, 0] = 0.0                                     # 0 times infinity is NaN
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref, scale = O.conv(x.astype(np.float64), nbr, W.astype(np.float64))
+    got = g.from_gpu_order(L.conv(g.to_gpu_order(x), to_dev(W)))
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    inf = np.isinf(ref)
+    assert inf.any() and np.isnan(ref).any() and np.array_equal(got[inf], ref[inf])
+    ok = np.isfinite(ref) & (np.abs(ref) < 3.4e38)
+    assert np.isfinite(got[ok]).all()
+    assert_close_scaled(got[ok], ref[ok], scale[ok], REL_F32, "conv with extreme values")
+    tiny = random_rows(lat.V, C_in, seed=1303) * np.float32(1e-28)
+    ref, scale = O.conv(tiny.astype(np.float64), nbr, W.astype(np.float64))
+    assert_close_scaled(g.from_gpu_order(L.conv(g.to_gpu_order(tiny), to_dev(W))), ref, scale, REL_F32, "tiny rows",
+                        atol=0.0)
+    L.close()
