@@ -21,8 +21,10 @@
 //
 // Weight gradient.  For each tap, dW_t [C_out x C_in] is a product whose
 // reduction runs over the V vertices: A = g^T (rows of g, contiguous) and
-// B = the gathered rows x_{nbr(v,t)}.  k_conv_wgrad gives each workgroup one
-// tap, one 64 x 64 tile of (output, input) channels and one chunk of the
+// B = the gathered rows x_{nbr(v,t)}.  k_conv_wgrad_taps (bf16 MFMA, three taps
+// a workgroup) covers channel counts that are multiples of 4 with aligned
+// rows, in bf16 and in fp32 on fp32 rows; k_conv_wgrad the rest: each workgroup
+// one tap, one 64 x 64 tile of (output, input) channels and one chunk of the
 // vertices (chunk c of nch covers rows [c V / nch, (c+1) V / nch), V read on
 // the device).  Per step of 32 vertices it stages the 32 g rows and the 32
 // gathered x rows in LDS as fp32 and four wavefronts each accumulate a
@@ -207,49 +209,102 @@ __global__ __launch_bounds__(kBlock) void k_conv_wgrad(const void *__restrict__ 
     }
 }
 
-// The bf16 computation on bf16 MFMA (v_mfma_f32_32x32x16_bf16): lane l
-// supplies A[l % 32][8 (l / 32) + 0..7] and B[8 (l / 32) + 0..7][l % 32],
-// eight consecutive K = vertex values per lane.  So the step's rows are
+// The weight gradient on bf16 MFMA (v_mfma_f32_32x32x16_bf16), for channel
+// counts that are multiples of 4 and aligned rows: bf16 products (CM 1), or
+// fp32 ones as the six largest products of three-term splits (CM 3, see
+// split3).  Lane l supplies A[l % 32][8 (l / 32) + 0..7] and B[8 (l / 32) +
+// 0..7][l % 32], eight consecutive K = vertex values.  So the step's rows are
 // staged transposed in LDS, channel-major with the 32 vertices of the step
-// contiguous (row stride kTRow bytes): each thread loads two consecutive
-// rows of four channels, packs the two bf16 values of each channel into one
-// word and stores it at [channel][vertex pair].  Products of bf16 values are
-// exact in fp32 and the sums are fp32, as in the fp32-MFMA kernel.
+// contiguous: each thread loads two consecutive rows of four channels, packs
+// the pair of each channel into one word (per plane) and stores it at
+// [channel][vertex pair].  At a pitch of 17 words those writes fall on 64
+// different banks.
+//
+// What bounds it is the latency of a step's gathers, not their bytes: a
+// workgroup takes kTaps taps of its chunk, so that a step's g rows are loaded
+// and staged once for three products, with two steps' rows in flight and two
+// workgroups per CU (a tap per workgroup, one step ahead and four per CU kept
+// fewer loads in flight and read g nine times).  With its reduction, us, that
+// kernel -> this one (fp32: fp32 MFMA 32x32x2 -> the split): V = 278 788, T = 9:
+// bf16 64 -> 64 119 -> 79, 128 -> 128 407 -> 262, fp32 64 -> 64 256 -> 167, 128 -> 128
+// 920 -> 579; V = 70 989: 41 -> 34, 113 -> 82, 78 -> 58, 245 -> 168; V = 5 211: 18.7 ->
+// 17.2, 23.9 -> 23.5, 23.5 -> 21.6, 36.7 -> 37.2.  The largest, bf16 128 -> 128, runs
+// at 313 TFLOP/s of the 2 400 the matrix cores reach: the transposing stores to
+// LDS and the gathers' latency.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef u32x4_t u32x4_a4_t __attribute__((aligned(4)));
 
 constexpr int kTStep = 32;   // vertices per step (two MFMA K-steps of 16)
-constexpr int kTRow = 80;    // LDS bytes per channel row: 32 bf16 + 16 bytes of padding
+constexpr int kTRow = 68;    // LDS bytes per channel row: 32 bf16 + 4 bytes of padding
+constexpr int kTaps = 3;     // taps per workgroup
 
-// Four consecutive channels [c, c+4) of row `row` as bf16 bits (rounded to
-// nearest even from fp32 storage), zero past C; C % 4 == 0 and aligned rows.
+// Four consecutive channels of a row as the products take them: bf16 bits
+// (rounded to nearest even from fp32 storage), or fp32.
+template <int CM, bool BF16>
+struct Row4;
 template <bool BF16>
-__device__ __forceinline__ uint2 load4_bf16(const void *base, int64_t row, int C, int c) {
-    if (c >= C) return make_uint2(0u, 0u);
-    if (BF16) return *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(base) + row * C + c);
-    const float4 f = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(base) + row * C + c);
-    return make_uint2(bf16_bits(f.x) | (bf16_bits(f.y) << 16), bf16_bits(f.z) | (bf16_bits(f.w) << 16));
+struct Row4<1, BF16> {
+    uint2 u;
+    __device__ __forceinline__ void load(const void *base, int64_t row, int C, int c) {
+        if (BF16) {
+            u = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(base) + row * C + c);
+        } else {
+            const float4 f = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(base) + row * C + c);
+            u = make_uint2(bf16_bits(f.x) | (bf16_bits(f.y) << 16), bf16_bits(f.z) | (bf16_bits(f.w) << 16));
+        }
+    }
+    __device__ __forceinline__ void zero() { u = make_uint2(0u, 0u); }
+};
+template <bool BF16>
+struct Row4<3, BF16> {
+    float f[4];
+    __device__ __forceinline__ void load(const void *base, int64_t row, int C, int c) {
+        const float4 t = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(base) + row * C + c);
+        f[0] = t.x;
+        f[1] = t.y;
+        f[2] = t.z;
+        f[3] = t.w;
+    }
+    __device__ __forceinline__ void zero() { f[0] = f[1] = f[2] = f[3] = 0.f; }
+};
+
+// Chunks that a launch of nch uses for V vertices: at least 2 tiles steps
+// each.  The host knows only the lattice's bound; the kernel and the reduction
+// both take this count, so that a lattice far below its bound does not write
+// and sum partials of a step or two.  A chunk's partial grows with the tiles,
+// and so does the step count at which its traffic is worth a workgroup
+// (V = 5211, T = 9, bf16: 32 -> 32 in chunks of 1, 4 and 8 steps 12.9, 14.0 and
+// 18.5 us; 128 -> 128 26.6, 26.5 and 23.4).
+__device__ __forceinline__ int chunks_used(int64_t V, int nch, int tiles) {
+    const int64_t n = V / (2 * tiles * kTStep) / 8 * 8;
+    return (int)(n < 8 ? (nch < 8 ? nch : 8) : n < nch ? n : (int64_t)nch);
 }
 
-template <bool G_BF16, bool X_BF16>
-__global__ __launch_bounds__(kBlock) void k_conv_wgrad_bf16(const void *__restrict__ g, int C_out,
-                                                            const void *__restrict__ x, int C_in, int T,
-                                                            const int32_t *__restrict__ nbr,
-                                                            const int32_t *__restrict__ counters, int nch,
-                                                            float *__restrict__ partial, float *__restrict__ pbias) {
-    __shared__ __attribute__((aligned(16))) char gs[kTile * kTRow];
-    __shared__ __attribute__((aligned(16))) char xs[kTile * kTRow];
+template <int CM, bool G_BF16, bool X_BF16>
+__global__ __launch_bounds__(kBlock, 2) void k_conv_wgrad_taps(const void *__restrict__ g, int C_out,
+                                                               const void *__restrict__ x, int C_in, int T,
+                                                               const int32_t *__restrict__ nbr,
+                                                               const int32_t *__restrict__ counters, int max_chunks,
+                                                               float *__restrict__ partial,
+                                                               float *__restrict__ pbias) {
+    constexpr int Z = CM == 3 ? 3 : 1;               // planes
+    constexpr int PLANE = kTile * kTRow;
+    __shared__ __attribute__((aligned(16))) char gs[Z * PLANE];
+    __shared__ __attribute__((aligned(16))) char xs[kTaps * Z * PLANE];
     __shared__ float bred[kBlock / 16][kTile];
 
     const int64_t V = counters[CNT_V];
     const int chunk = blockIdx.x;
-    const int t = blockIdx.y;
+    const int nch = chunks_used(V, max_chunks, gridDim.z);
+    if (chunk >= nch) return;
+    const int t0 = blockIdx.y * kTaps;
     const int tiles_i = (C_in + kTile - 1) / kTile;
     const int o0 = (blockIdx.z / tiles_i) * kTile;
     const int i0 = (blockIdx.z % tiles_i) * kTile;
     const int64_t lo = V * chunk / nch;
     const int64_t hi = V * (chunk + 1) / nch;
-    const bool do_bias = pbias != nullptr && t == 0 && i0 == 0;
+    const bool do_bias = pbias != nullptr && t0 == 0 && i0 == 0;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -260,27 +315,37 @@ __global__ __launch_bounds__(kBlock) void k_conv_wgrad_bf16(const void *__restri
     // Loader mapping: channel chunk c4 (4 channels), rows 2 rp and 2 rp + 1 of the step.
     const int c4 = (tid & 15) * 4;
     const int rp = tid >> 4;
+    const bool g_in = o0 + c4 < C_out, x_in = i0 + c4 < C_in;
 
-    f32x16_t acc;
+    f32x16_t acc[kTaps];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int k = 0; k < kTaps; ++k)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[k][r] = 0.f;
     float bsum[4] = {0.f, 0.f, 0.f, 0.f};
 
-    uint2 ga[2], xa[2];
-    int32_t ua[2];
+    // the rows of two steps (slot: step mod 2), and the next step's indices
+    Row4<CM, G_BF16> ga[2][2];
+    Row4<CM, X_BF16> xa[2][kTaps][2];
+    int32_t un[kTaps][2];
     auto load_index = [&](int64_t k0) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int64_t v = k0 + 2 * rp + j;
-            ua[j] = v < hi ? nbr[v * T + t] : -1;
+#pragma unroll
+            for (int k = 0; k < kTaps; ++k) un[k][j] = v < hi && t0 + k < T ? nbr[v * T + t0 + k] : -1;
         }
     };
-    auto load_step = [&](int64_t k0) {
+    auto load_step = [&](int64_t k0, int s) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int64_t v = k0 + 2 * rp + j;
-            ga[j] = v < hi ? load4_bf16<G_BF16>(g, v, C_out, o0 + c4) : make_uint2(0u, 0u);
-            xa[j] = ua[j] >= 0 ? load4_bf16<X_BF16>(x, ua[j], C_in, i0 + c4) : make_uint2(0u, 0u);
+            if (v < hi && g_in) ga[s][j].load(g, v, C_out, o0 + c4);
+            else ga[s][j].zero();
+#pragma unroll
+            for (int k = 0; k < kTaps; ++k)
+                if (un[k][j] >= 0 && x_in) xa[s][k][j].load(x, un[k][j], C_in, i0 + c4);
+                else xa[s][k][j].zero();
         }
     };
     // the bias sums the output gradient as stored (fp32 rows unrounded)
@@ -288,63 +353,114 @@ __global__ __launch_bounds__(kBlock) void k_conv_wgrad_bf16(const void *__restri
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int64_t v = k0 + 2 * rp + j;
-            if (v >= hi || o0 + c4 >= C_out) continue;
-            if (G_BF16) {
-                const uint2 u = ga[j];
-                bsum[0] += __uint_as_float(u.x << 16);
-                bsum[1] += __uint_as_float(u.x & 0xffff0000u);
-                bsum[2] += __uint_as_float(u.y << 16);
-                bsum[3] += __uint_as_float(u.y & 0xffff0000u);
-            } else {
-                const float4 f =
-                    *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(g) + v * C_out + o0 + c4);
-                bsum[0] += f.x;
-                bsum[1] += f.y;
-                bsum[2] += f.z;
-                bsum[3] += f.w;
+            if (v >= hi || !g_in) continue;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t at = v * C_out + o0 + c4 + e;
+                bsum[e] += G_BF16 ? bf16_to_f32(reinterpret_cast<const uint16_t *>(g)[at])
+                                  : reinterpret_cast<const float *>(g)[at];
             }
         }
     };
-    if (lo < hi) {
-        load_index(lo);
-        load_step(lo);
-        load_index(lo + kTStep);
-    }
-    for (int64_t k0 = lo; k0 < hi; k0 += kTStep) {
-        if (do_bias) add_bias(k0);
-        // registers -> LDS: word e of a thread = channel c4 + e of rows 2 rp, 2 rp + 1
+    // registers -> LDS: word e of a thread = channel c4 + e of rows 2 rp, 2 rp + 1
+    auto put = [&](char *base, const auto &r0, const auto &r1) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int sh = (e & 1) * 16;
-            const uint32_t gw = ((((e < 2) ? ga[0].x : ga[0].y) >> sh) & 0xffffu) |
-                                ((((e < 2) ? ga[1].x : ga[1].y) >> sh) << 16);
-            const uint32_t xw = ((((e < 2) ? xa[0].x : xa[0].y) >> sh) & 0xffffu) |
-                                ((((e < 2) ? xa[1].x : xa[1].y) >> sh) << 16);
-            *reinterpret_cast<uint32_t *>(gs + (c4 + e) * kTRow + 4 * rp) = gw;
-            *reinterpret_cast<uint32_t *>(xs + (c4 + e) * kTRow + 4 * rp) = xw;
+            char *at = base + (c4 + e) * kTRow + 4 * rp;
+            if constexpr (CM == 3) {
+                uint32_t hh, mm, ll;
+                split3(r0.f[e], r1.f[e], hh, mm, ll);
+                *reinterpret_cast<uint32_t *>(at) = hh;
+                *reinterpret_cast<uint32_t *>(at + PLANE) = mm;
+                *reinterpret_cast<uint32_t *>(at + 2 * PLANE) = ll;
+            } else {
+                const int sh = (e & 1) * 16;
+                *reinterpret_cast<uint32_t *>(at) = (((e < 2 ? r0.u.x : r0.u.y) >> sh) & 0xffffu) |
+                                                    (((e < 2 ? r1.u.x : r1.u.y) >> sh) << 16);
+            }
         }
-        __syncthreads();
-        if (k0 + kTStep < hi) {
-            load_step(k0 + kTStep);
-            load_index(k0 + 2 * kTStep);
-        }
+    };
+    auto step = [&](int64_t k0, int s) {
+        if (do_bias) add_bias(k0);
+        put(gs, ga[s][0], ga[s][1]);
 #pragma unroll
-        for (int s = 0; s < kTStep / 16; ++s) {
-            const u32x4_t a = *reinterpret_cast<const u32x4_t *>(gs + (ow + (lane & 31)) * kTRow + 32 * s + 16 * h);
-            const u32x4_t b = *reinterpret_cast<const u32x4_t *>(xs + (iw + (lane & 31)) * kTRow + 32 * s + 16 * h);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a),
-                                                          __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
+        for (int k = 0; k < kTaps; ++k) put(xs + k * Z * PLANE, xa[s][k][0], xa[s][k][1]);
+        __syncthreads();
+        load_step(k0 + 2 * kTStep, s);
+        load_index(k0 + 3 * kTStep);
+#pragma unroll
+        for (int q = 0; q < kTStep / 16; ++q) {
+            const int at = (lane & 31) * kTRow + 32 * q + 16 * h;
+            u32x4_t a[Z];
+#pragma unroll
+            for (int z = 0; z < Z; ++z) a[z] = *reinterpret_cast<const u32x4_a4_t *>(gs + z * PLANE + ow * kTRow + at);
+#pragma unroll
+            for (int k = 0; k < kTaps; ++k) {
+                u32x4_t b[Z];
+#pragma unroll
+                for (int z = 0; z < Z; ++z)
+                    b[z] = *reinterpret_cast<const u32x4_a4_t *>(xs + (k * Z + z) * PLANE + iw * kTRow + at);
+                constexpr int NP = CM == 3 ? 6 : 1;
+                constexpr int za[6] = {0, 2, 1, 0, 1, 0}, zb[6] = {2, 0, 1, 1, 0, 0};  // smallest first
+#pragma unroll
+                for (int p = 0; p < NP; ++p)
+                    acc[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        __builtin_bit_cast(bf16x8_t, a[CM == 3 ? za[p] : 0]),
+                        __builtin_bit_cast(bf16x8_t, b[CM == 3 ? zb[p] : 0]), acc[k], 0, 0, 0);
+            }
         }
         __syncthreads();
+    };
+    if (lo < hi) {
+        load_index(lo);
+        load_step(lo, 0);
+        load_index(lo + kTStep);
+        load_step(lo + kTStep, 1);
+        load_index(lo + 2 * kTStep);
+    }
+    for (int64_t k0 = lo; k0 < hi; k0 += 2 * kTStep) {
+        step(k0, 0);
+        if (k0 + kTStep < hi) step(k0 + kTStep, 1);
     }
 
-    float *dst = partial + (int64_t)chunk * C_out * T * C_in;
+    // element r of acc: output channel 8 (r / 4) + 4 h + r % 4, input channel l % 32
     const int ic = i0 + iw + (lane & 31);
+    auto oc_of = [&](int r) { return o0 + ow + 8 * (r >> 2) + 4 * h + (r & 3); };
+    if constexpr (CM == 3) {
+        // a sum that is not finite may come from a value too large for the
+        // split, or not finite itself: this wavefront's sums once more, as
+        // chains of fp32 FMAs
+        bool bad = false;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int oc = o0 + ow + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (oc < C_out && ic < C_in) dst[((int64_t)oc * T + t) * C_in + ic] = acc[r];
+        for (int k = 0; k < kTaps; ++k)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) bad |= !(fabsf(acc[k][r]) <= 3.402823466e38f);
+        if (__ballot(bad) != 0ull) {
+#pragma unroll
+            for (int k = 0; k < kTaps; ++k)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    float y = 0.f;
+                    const int oc = oc_of(r);
+                    if (oc < C_out && ic < C_in && t0 + k < T)
+                        for (int64_t v = lo; v < hi; ++v) {
+                            const int u = nbr[v * T + t0 + k];
+                            if (u >= 0)
+                                y = fmaf(reinterpret_cast<const float *>(g)[v * C_out + oc],
+                                         reinterpret_cast<const float *>(x)[(int64_t)u * C_in + ic], y);
+                        }
+                    acc[k][r] = y;
+                }
+        }
     }
+    float *dst = partial + (int64_t)chunk * C_out * T * C_in;
+#pragma unroll
+    for (int k = 0; k < kTaps; ++k)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int oc = oc_of(r);
+            if (oc < C_out && ic < C_in && t0 + k < T) dst[((int64_t)oc * T + t0 + k) * C_in + ic] = acc[k][r];
+        }
     if (do_bias) {
         // threads tid and tid + 16 k (k = 0..15) share channel chunk c4
 #pragma unroll
@@ -363,9 +479,11 @@ __global__ __launch_bounds__(kBlock) void k_conv_wgrad_bf16(const void *__restri
 // chunks c = g, g+4, g+8, ... (g = wavefront) with four loads in flight, and
 // the four group sums are added in group order.
 constexpr int kRedCols = 64;
-__global__ __launch_bounds__(kBlock) void k_wgrad_reduce(const float *__restrict__ part, int nch, int64_t n,
-                                                         float *__restrict__ out) {
+__global__ __launch_bounds__(kBlock) void k_wgrad_reduce(const float *__restrict__ part,
+                                                         const int32_t *__restrict__ counters, int nch, int tiles,
+                                                         int64_t n, float *__restrict__ out) {
     __shared__ float red[kBlock / kRedCols][kRedCols];
+    if (counters) nch = chunks_used(counters[CNT_V], nch, tiles);
     const int g = threadIdx.x / kRedCols;
     const int64_t j = (int64_t)blockIdx.x * kRedCols + (threadIdx.x % kRedCols);
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
@@ -408,14 +526,26 @@ __global__ __launch_bounds__(kBlock) void k_flip_weights(const E *__restrict__ w
 
 }  // namespace
 
-// Number of vertex chunks of the weight gradient: about kWgPerCu workgroups
-// per CU over all taps and tiles, a multiple of 8 (the chunk's workgroups of
-// every tap then share one XCD's L2), and no more chunks than steps of 64
-// rows in the largest lattice.
+// Number of vertex chunks of the weight gradient, a multiple of 8 (the
+// chunk's workgroups of every tap then share one XCD's L2) and no more than
+// steps of 32 rows in the largest lattice.  One tap per workgroup: about
+// kWgPerCu workgroups per CU over all taps and tiles.  kTaps per workgroup:
+// about two per CU, as far as the partials stay within the allocation-free
+// call's workspace (where the first count's do; else that count, so that
+// the same shapes fit it).
 int wgrad_chunks(const lattice *L, int C_in, int C_out) {
-    const int64_t tiles = (int64_t)((C_out + kTile - 1) / kTile) * ((C_in + kTile - 1) / kTile) * L->T;
-    int64_t nch = (kWgPerCu * (int64_t)L->cu_count + tiles - 1) / tiles;
-    nch = (nch + 7) / 8 * 8;
+    const int64_t tiles = (int64_t)((C_out + kTile - 1) / kTile) * ((C_in + kTile - 1) / kTile);
+    const int64_t per = (kWgPerCu * (int64_t)L->cu_count + tiles * L->T - 1) / (tiles * L->T);
+    int64_t nch = (per + 7) / 8 * 8;
+    const int64_t n = (int64_t)C_out * L->T * C_in;
+    const int64_t room = LATTICE_NOALLOC_WORKSPACE_BYTES - (n * 4 + 255) / 256 * 256;
+    const int64_t fit = room / ((n + C_out) * 4) / 8 * 8;
+    // rounded down: 528 workgroups over 512 places took a second round (fp32
+    // 32 -> 32 on V = 278 788 246 us against 167 for 64 -> 64)
+    int64_t want = 2 * (int64_t)L->cu_count / (tiles * ((L->T + kTaps - 1) / kTaps)) / 8 * 8;
+    if (want > fit) want = fit;
+    if (want < 8) want = 8;
+    if (nch <= fit) nch = want;
     const int64_t steps = (L->max_vertices + kStep - 1) / kStep;
     if (nch > steps) nch = steps;
     if (nch < 1) nch = 1;
@@ -431,20 +561,19 @@ hipError_t launch_conv_wgrad(lattice *L, const void *g, lattice_dtype g_dt, int 
                      (reinterpret_cast<uintptr_t>(x) & (xb ? 7 : 15)) == 0;
     const dim3 grid((unsigned)nch, (unsigned)L->T,
                     (unsigned)(((C_out + kTile - 1) / kTile) * ((C_in + kTile - 1) / kTile)));
-    if (rnd && vec) {
-        // bf16 computation on bf16 MFMA
-        if (gb && xb)
-            hipLaunchKernelGGL((k_conv_wgrad_bf16<true, true>), grid, dim3(kBlock), 0, L->stream, g, C_out, x, C_in,
-                               L->T, L->nbr, L->counters, nch, partial, grad_bias ? pbias : nullptr);
-        else if (gb)
-            hipLaunchKernelGGL((k_conv_wgrad_bf16<true, false>), grid, dim3(kBlock), 0, L->stream, g, C_out, x, C_in,
-                               L->T, L->nbr, L->counters, nch, partial, grad_bias ? pbias : nullptr);
-        else if (xb)
-            hipLaunchKernelGGL((k_conv_wgrad_bf16<false, true>), grid, dim3(kBlock), 0, L->stream, g, C_out, x, C_in,
-                               L->T, L->nbr, L->counters, nch, partial, grad_bias ? pbias : nullptr);
-        else
-            hipLaunchKernelGGL((k_conv_wgrad_bf16<false, false>), grid, dim3(kBlock), 0, L->stream, g, C_out, x,
-                               C_in, L->T, L->nbr, L->counters, nch, partial, grad_bias ? pbias : nullptr);
+    const int32_t *used = nullptr;  // the counters, where the kernel leaves chunks out
+    if (vec && (rnd || (!gb && !xb))) {
+        used = L->counters;
+        const dim3 grid3(grid.x, (unsigned)((L->T + kTaps - 1) / kTaps), grid.z);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, grid3, dim3(kBlock), 0, L->stream, g, C_out, x, C_in, L->T, L->nbr, L->counters,
+                               nch, partial, grad_bias ? pbias : nullptr);
+        };
+        if (!rnd) go(k_conv_wgrad_taps<3, false, false>);
+        else if (gb && xb) go(k_conv_wgrad_taps<1, true, true>);
+        else if (gb) go(k_conv_wgrad_taps<1, true, false>);
+        else if (xb) go(k_conv_wgrad_taps<1, false, true>);
+        else go(k_conv_wgrad_taps<1, false, false>);
     } else {
 #define WG(GB, XB, RN, VC)                                                                                      \
     hipLaunchKernelGGL((k_conv_wgrad<GB, XB, RN, VC>), grid, dim3(kBlock), 0, L->stream, g, C_out, x, C_in, L->T, \
@@ -471,12 +600,13 @@ hipError_t launch_conv_wgrad(lattice *L, const void *g, lattice_dtype g_dt, int 
     if (grad_w) {
         const int64_t n = (int64_t)C_out * L->T * C_in;
         hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((n + kRedCols - 1) / kRedCols)), dim3(kBlock), 0,
-                           L->stream, partial, nch, n, grad_w);
+                           L->stream, partial, used, nch, (int)grid.z, n, grad_w);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (grad_bias) {
         hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((C_out + kRedCols - 1) / kRedCols)), dim3(kBlock), 0,
-                           L->stream, pbias, nch, (int64_t)C_out, grad_bias);
+                           L->stream, pbias, used, nch, (int)grid.z, (int64_t)C_out,
+                           grad_bias);
         e = hipGetLastError();
     }
     return e;

@@ -353,3 +353,52 @@ def test_backward_stages_at_partseg_size():
     gf, gf_s = O.splat_backward(lat, gx0)
     gf_d = L.splat_backward(g.to_gpu_order(gx0))
     assert_close_scaled(gf_d.cpu().numpy(), gf, gf_s, REL_F32, "partseg splat backward")
+
+
+@pytest.mark.parametrize("d,C_in,C_out,dtype,m", [
+    (3, 8, 16, "f32", 700), (3, 36, 100, "f32", 20000), (4, 128, 68, "f32", 3000), (2, 64, 64, "f32", 40),
+    (3, 36, 100, "bf16", 20000), (4, 4, 132, "bf16", 3000), (2, 96, 96, "bf16", 40)])
+def test_conv_weight_gradient_shapes(d, C_in, C_out, dtype, m):
+    """The tap-grouped weight gradient off its tiles: channel counts that do
+    not fill a 64 x 64 tile, 7, 9 and 11 taps (a last group of one, three and
+    two), fewer vertices than one step and chunks of an odd number of steps.
+    fp32 rows also with infinities, NaN and values beyond bf16's largest:
+    the entries they do not reach keep the usual accuracy, the others are
+    infinite or NaN where the sum of the same products is."""
+    w = random_cloud(m, d, seed=1400 + d, extent=1.0, C=1)
+    L = _lattice(d, 0.25, w.m)
+    g = GpuLattice(L, w.pos, w.feat)
+    lat = O.build(w.pos, 0.25)
+    nbr = O.neighbors(lat)
+    x = random_rows(lat.V, C_in, seed=1401)
+    go = random_rows(lat.V, C_out, seed=1402, std=0.1)      # 0.1: the largest products stay finite in fp32
+    W = conv_weight(C_in, C_out, d, seed=1403)
+    wd = to_dev(W)
+    if dtype == "bf16":
+        x, go, wd = O.round_bf16(x), O.round_bf16(go), L.weights_to_bf16(wd)
+
+    def both():
+        got = L.conv_backward(g.to_gpu_order(go), wd, g.to_gpu_order(x), dtype=dtype, want_input=False)[1]
+        ref = np.zeros(W.shape)
+        scale = np.zeros(W.shape)
+        for t in range(nbr.shape[1]):
+            on = nbr[:, t] >= 0
+            gt, xt = go[on].astype(np.float64), x[nbr[on, t]].astype(np.float64)
+            ref[:, t] = gt.T @ xt
+            scale[:, t] = np.abs(gt).T @ np.abs(xt)
+        return got.cpu().numpy().astype(np.float64), ref, scale
+
+    got, ref, scale = both()
+    assert_close_scaled(got, ref, scale, REL_F32, "weight gradient")
+    if dtype == "f32":
+        x[0, 0], x[lat.V // 2, 1], x[lat.V - 1, 2], go[0, 1] = np.inf, np.nan, 3.39e38, -np.inf
+        with np.errstate(invalid="ignore", over="ignore"):
+            got, ref, scale = both()
+        assert np.array_equal(np.isnan(got), np.isnan(ref))
+        ok = np.isfinite(ref)
+        assert np.abs(ref[ok]).max() < 3.0e38
+        assert ok.any() and np.isfinite(got[ok]).all()
+        assert_close_scaled(got[ok], ref[ok], scale[ok], REL_F32, "weight gradient beside extreme values")
+        inf = np.isinf(ref)
+        assert inf.any() and np.array_equal(got[inf], ref[inf])
+    L.close()
