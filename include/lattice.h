@@ -194,8 +194,10 @@ lattice_status lattice_conv(lattice *L, const void *in, lattice_dtype in_dtype, 
  * calls (the result is the same to the stated tolerances; this is for
  * testing and benchmarking each kernel).
  *   LATTICE_CONV_AUTO    the fastest kernel built for the shape (default)
- *   LATTICE_CONV_TILED   the LDS-tiled kernel (weights and gathered rows
- *                        staged per K chunk), else the any-shape one
+ *   LATTICE_CONV_TILED   the LDS-tiled kernels (weights and gathered rows
+ *                        staged per K chunk), else the any-shape one; fp32
+ *                        on fp32 matrix instructions where the 64-wide tiles
+ *                        cover the shape
  *   LATTICE_CONV_WS      weight slice resident in LDS, rows gathered straight
  *                        into registers, where built for the shape; else TILED
  *   LATTICE_CONV_RS      weights resident in registers, rows gathered into
@@ -552,8 +554,8 @@ lattice_status lattice_distribute_pointnet(lattice *L, const float *pos, const f
  *   grad_params  dev fp32 output in the layout of params (per block:
  *                d(gamma or a) [K], d(beta or s) [K], dW [w][K], db [w]);
  *                must not overlap params.
- * The first call grows the lattice's scratch for it (a record of 512 bytes
- * per pair and the partial sums).  Returns as the forward, and
+ * The first call grows the lattice's scratch for it (512 bytes per pair and
+ * the partial sums).  Returns as the forward, and
  * LATTICE_E_ARG for a missing grad_out or grad_params.
  */
 lattice_status lattice_distribute_pointnet_backward(lattice *L, const float *pos, const float *feat, int f_d,

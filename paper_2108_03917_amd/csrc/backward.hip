@@ -545,7 +545,7 @@ int wgrad_chunks(const lattice *L, int C_in, int C_out) {
     int64_t want = 2 * (int64_t)L->cu_count / (tiles * ((L->T + kTaps - 1) / kTaps)) / 8 * 8;
     if (want > fit) want = fit;
     if (want < 8) want = 8;
-    if (nch <= fit) nch = want;
+    if (nch <= fit && C_in % 4 == 0 && C_out % 4 == 0) nch = want;
     const int64_t steps = (L->max_vertices + kStep - 1) / kStep;
     if (nch > steps) nch = steps;
     if (nch < 1) nch = 1;
@@ -578,20 +578,24 @@ hipError_t launch_conv_wgrad(lattice *L, const void *g, lattice_dtype g_dt, int 
 #define WG(GB, XB, RN, VC)                                                                                      \
     hipLaunchKernelGGL((k_conv_wgrad<GB, XB, RN, VC>), grid, dim3(kBlock), 0, L->stream, g, C_out, x, C_in, L->T, \
                        L->nbr, L->counters, nch, partial, grad_bias ? pbias : nullptr)
-#define WG_V(GB, XB, RN) \
-    if (vec)             \
-        WG(GB, XB, RN, true); \
-    else                 \
-        WG(GB, XB, RN, false)
-    if (gb) {
-        if (xb) { WG_V(true, true, true); }
-        else if (rnd) { WG_V(true, false, true); }
-        else { WG_V(true, false, false); }
-    } else {
-        if (xb) { if (rnd) { WG_V(false, true, true); } else { WG_V(false, true, false); } }
-        else if (rnd) { WG_V(false, false, true); }
-        else { WG_V(false, false, false); }
-    }
+#define WG_V(GB, XB) \
+    if (vec)         \
+        WG(GB, XB, false, true); \
+    else             \
+        WG(GB, XB, false, false)
+        // bf16 products here have odd widths or unaligned rows, fp32 ones
+        // those or bf16 rows
+        if (gb) {
+            if (xb && rnd) WG(true, true, true, false);
+            else if (xb) { WG_V(true, true); }
+            else if (rnd) WG(true, false, true, false);
+            else { WG_V(true, false); }
+        } else {
+            if (xb && rnd) WG(false, true, true, false);
+            else if (xb) { WG_V(false, true); }
+            else if (rnd) WG(false, false, true, false);
+            else WG(false, false, false, false);
+        }
 #undef WG_V
 #undef WG
     }
