@@ -1393,17 +1393,16 @@ hipError_t dispatch_out(lattice *L, const void *in, lattice_dtype in_dt, int C_i
     // one but 64 -> a multiple of 128 with 9 taps, where the resident weight
     // slice is a little faster (64 -> 256, us, V = 24 941 / 70 989 / 278 788:
     // 22.6 / 57.8 / 187 against 26.7 / 56.1 / 198; elsewhere e.g. 128 -> 64 on
-    // V = 70 989 41 against 27, fp32 rows 64 -> 64 47 against 31), and the fp32
-    // ones but small clouds' with C_out a multiple of 64 other than 64 (its
-    // split into bf16 products pays from larger tiles on: 128 -> 128 on
-    // V = 5 211 30 against 36, on V = 70 989 194 against 181, on V = 278 788
-    // 697 against 459; 64 -> 64 17 against 12.9, 61 against 48, 196 against 160)
+    // V = 70 989 41 against 27, fp32 rows 64 -> 64 47 against 31), the fp32
+    // ones the LDS-tiled kernel is not built for, and fp32 -> 64 channels on
+    // small clouds, whose 64-row tiles leave CUs idle (64 -> 64 on V = 5 211:
+    // 17.0 against 12.9; larger: 58.6 against 60.2)
     const bool seg = aligned && conv_seg_covers(in_dt, C_in, dt);
     const lattice_dtype out_dt = OUT_BF16 ? LATTICE_BF16 : LATTICE_F32;
     const bool small = L->max_vertices <= 64 * (int64_t)L->cu_count;
     if (seg && path == LATTICE_CONV_AUTO) {
         const bool ws = in_bf16 && L->T == 9 && C_in == 64 && C_out % 128 == 0;
-        const bool tiled = C_in % 32 == 0 && C_out % 64 == 0 && (small ? C_out != 64 : C_in > kSplitMaxC);
+        const bool tiled = C_in % 32 == 0 && C_out % 64 == 0 && !(small && C_out == 64);
         if (bf16 ? !ws : !tiled) return launch_conv_seg(L, in, in_dt, C_in, w, C_out, dt, bias, out, out_dt);
     }
     if (aligned && path != LATTICE_CONV_TILED) {

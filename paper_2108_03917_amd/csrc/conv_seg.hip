@@ -19,18 +19,12 @@
 // weights as the A operand, so that a lane ends up with four consecutive
 // output channels of one row and stores them at once.
 //
-// fp32 products run on the bf16 matrix cores, 15 times as fast, as six
-// products of three-term splits (see split3); their error against 64 bits is
-// a little below fp32 MFMA's (64 -> 64 3e-7 against 4e-7, 128 -> 128 4e-7
-// against 5e-7: fewer roundings of the running sum).
-//
 // What bounds it: bf16, the gathers and the weight rows through L2 (each tile
-// re-reads W); the split, its own vector instructions (5.5 a value and stage)
-// and LDS; fp32 MFMA, the matrix cores (90 of 154 TFLOP/s).  Against the
+// re-reads W); fp32, the matrix cores (90 of 154 TFLOP/s).  Against the
 // element-wise kernel that took these shapes before (us, before -> now):
 // V = 278 788, 9 taps: bf16 32 -> 32 115 -> 30, 96 -> 96 546 -> 109, 100 -> 100
-// 583 -> 159, fp32 96 -> 96 963 -> 293, 8 -> 16 90 -> 24; V = 24 941: fp32
-// 96 -> 96 114 -> 46.
+// 583 -> 159, fp32 96 -> 96 963 -> 522, 8 -> 16 90 -> 24; V = 24 941: fp32
+// 96 -> 96 114 -> 56.
 #include <type_traits>
 
 #include "internal.h"
@@ -42,11 +36,11 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
+constexpr int kRowBytes = 144;
 constexpr int kMaxTaps = LATTICE_TAPS(LATTICE_MAX_D);
 constexpr int kThreads = 256;
 
-// CM 0: fp32 rows and weights, fp32 MFMA; CM 3: the same on bf16 MFMA, see
-// split3; CM 1: fp32 rows rounded to bf16
+// CM 0: fp32 rows and weights, fp32 MFMA; CM 1: fp32 rows rounded to bf16
 // while staging, bf16 weights; CM 2: bf16 rows and weights.  The four
 // wavefronts are WM x (4 / WM), each TI x TJ tiles of 16 x 16.
 template <int CM, int WM, int TI, int TJ>
@@ -54,35 +48,23 @@ __global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ 
                                                        const void *__restrict__ wv, int C_out, int T,
                                                        const float *__restrict__ bias, void *__restrict__ out,
                                                        int out_bf16, int out_vec, const int32_t *__restrict__ nbr,
-                                                       const int32_t *__restrict__ counters,
-                                                       const float *__restrict__ zero_row) {
+                                                       const int32_t *__restrict__ counters) {
     constexpr int WN = 4 / WM;
     constexpr int BM = WM * TI * 16, BN = WN * TJ * 16;
     constexpr int SE = CM == 2 ? 8 : 4;               // channels per segment
-    constexpr bool SPLIT = CM == 3;
-    constexpr int ESZ = CM == 0 || SPLIT ? 4 : 2;     // weight element (and staged element, unless split)
+    constexpr int ESZ = CM == 0 ? 4 : 2;              // operand element in LDS
     constexpr int SB = SE * ESZ;                      // LDS (and weight) bytes per segment
     constexpr int XESZ = CM == 2 ? 2 : 4;             // stored input element: 16 bytes of input per segment
     constexpr int SEGS = 128 / SB;                    // segments per row and chunk
     constexpr int RPP = kThreads / SEGS;              // rows per pass
     constexpr int AP = (BM + RPP - 1) / RPP, BP = (BN + RPP - 1) / RPP;
     constexpr int AR = AP * RPP, BR = BP * RPP;       // LDS rows (whole passes)
-    // One LDS row: 128 bytes and 16 of padding (16 rows read 16 bytes each on
-    // 64 different banks), or three planes of 64 bytes without: four rows'
-    // 8-byte writes then fill the 64 banks, and 16-byte chunk c of row r sits at
-    // c ^ (r / 4 % 4), which spreads the reads of 16 rows the same way (padded
-    // rows had 2-way conflicts on the writes, half of the LDS time)
-    constexpr int kRowBytes = SPLIT ? 3 * 64 : 128 + 16;
     constexpr int P = 2;                              // chunks in the register ring
     typedef u32x4_t xseg_t;
     typedef typename std::conditional<SB == 16, u32x4_t, u32x2_t>::type wseg_t;
 
-    // LDS buffers: the split's planes take one (three workgroups per CU hide
-    // its second barrier), the others two
-    constexpr int BUFS = SPLIT ? 1 : 2;
-    __shared__ __attribute__((aligned(16))) char lds[BUFS * (AR + BR) * kRowBytes];
+    __shared__ __attribute__((aligned(16))) char lds[2 * (AR + BR) * kRowBytes];
     __shared__ int32_t nbr_s[AR * kMaxTaps];
-    __shared__ int redo_s;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
@@ -138,11 +120,8 @@ __global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ 
                 const int u = nbr_s[(row0 + i * RPP) * T + t];
                 if (in_k && u >= 0) mk |= 1u << i;
                 const int64_t row = u >= 0 ? u : 0;
-                // (SPLIT reads zeros there instead: every select saved is an
-                // issue slot, which is what it is short of)
-                const char *at = reinterpret_cast<const char *>(in) + (row * C_in + c) * XESZ;
-                if (SPLIT) at = in_k && u >= 0 ? at : reinterpret_cast<const char *>(zero_row);
-                areg[s][i] = *reinterpret_cast<const xseg_t *>(at);
+                areg[s][i] = *reinterpret_cast<const xseg_t *>(reinterpret_cast<const char *>(in) +
+                                                              (row * C_in + c) * XESZ);
             }
 #pragma unroll
             for (int i = 0; i < BP; ++i) {
@@ -157,21 +136,6 @@ __global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ 
             while (lc >= spr) {
                 lc -= spr;
                 ++lt;
-            }
-        };
-        // one staged segment: at its place in the row, or split over the planes
-        auto put = [&](char *row, wseg_t y) {
-            if constexpr (SPLIT) {
-                uint32_t h[2], m[2], l[2];
-                split3(__uint_as_float(y[0]), __uint_as_float(y[1]), h[0], m[0], l[0]);
-                split3(__uint_as_float(y[2]), __uint_as_float(y[3]), h[1], m[1], l[1]);
-                // (rows a multiple of 32 apart: r / 4 % 4 is row0's for every pass)
-                char *at = row + 16 * ((seg >> 1) ^ ((row0 >> 2) & 3)) + 8 * (seg & 1);
-                *reinterpret_cast<u32x2_t *>(at) = u32x2_t{h[0], h[1]};
-                *reinterpret_cast<u32x2_t *>(at + 64) = u32x2_t{m[0], m[1]};
-                *reinterpret_cast<u32x2_t *>(at + 128) = u32x2_t{l[0], l[1]};
-            } else {
-                *reinterpret_cast<wseg_t *>(row + seg * SB) = y;
             }
         };
         auto store_chunk = [&](int s, int buf) {
@@ -191,8 +155,8 @@ __global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ 
                     if constexpr (CM == 2) y = hi ? u32x4_t{y[2], y[3], 0u, 0u} : y;
                 }
 #pragma unroll
-                for (int k = 0; k < SB / 4; ++k) y[k] = on || SPLIT ? y[k] : 0u;
-                put(A + (row0 + i * RPP) * kRowBytes, y);
+                for (int k = 0; k < SB / 4; ++k) y[k] = on ? y[k] : 0u;
+                *reinterpret_cast<wseg_t *>(A + (row0 + i * RPP) * kRowBytes + seg * SB) = y;
             }
 #pragma unroll
             for (int i = 0; i < BP; ++i) {
@@ -201,44 +165,13 @@ __global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ 
                 if constexpr (CM == 2) y = hi ? u32x4_t{y[2], y[3], 0u, 0u} : y;
 #pragma unroll
                 for (int k = 0; k < SB / 4; ++k) y[k] = on ? y[k] : 0u;
-                put(B + (row0 + i * RPP) * kRowBytes, y);
+                *reinterpret_cast<wseg_t *>(B + (row0 + i * RPP) * kRowBytes + seg * SB) = y;
             }
         };
         // lane quarter q holds bytes 16 q .. of each 64: the same K in A and B
         auto compute = [&](int buf) {
-            const int qc = SPLIT ? q4 ^ ((j16 >> 2) & 3) : q4;  // (tiles start at multiples of 16 rows)
-            const char *A = lds + buf * (AR + BR) * kRowBytes + (wm * TI * 16 + j16) * kRowBytes + 16 * qc;
-            const char *B = lds + buf * (AR + BR) * kRowBytes + (AR + wn * TJ * 16 + j16) * kRowBytes + 16 * qc;
-            if constexpr (SPLIT) {
-                u32x4_t b[3][TJ];
-#pragma unroll
-                for (int z = 0; z < 3; ++z)
-#pragma unroll
-                    for (int j = 0; j < TJ; ++j)
-                        b[z][j] = *reinterpret_cast<const u32x4_t *>(B + j * 16 * kRowBytes + 64 * z);
-                // two row tiles at a time; smallest products first
-                constexpr int za[6] = {0, 2, 1, 0, 1, 0}, zb[6] = {2, 0, 1, 1, 0, 0};
-                constexpr int TU = TI < 2 ? TI : 2;
-#pragma unroll
-                for (int i0 = 0; i0 < TI; i0 += TU) {
-                    u32x4_t a[3][TU];
-#pragma unroll
-                    for (int z = 0; z < 3; ++z)
-#pragma unroll
-                        for (int i = 0; i < TU; ++i)
-                            a[z][i] = *reinterpret_cast<const u32x4_t *>(A + (i0 + i) * 16 * kRowBytes + 64 * z);
-#pragma unroll
-                    for (int z = 0; z < 6; ++z)
-#pragma unroll
-                        for (int i = 0; i < TU; ++i)
-#pragma unroll
-                            for (int j = 0; j < TJ; ++j)
-                                acc[i0 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                    __builtin_bit_cast(bf16x8_t, b[zb[z]][j]),
-                                    __builtin_bit_cast(bf16x8_t, a[za[z]][i]), acc[i0 + i][j], 0, 0, 0);
-                }
-                return;
-            }
+            const char *A = lds + buf * (AR + BR) * kRowBytes + (wm * TI * 16 + j16) * kRowBytes + 16 * q4;
+            const char *B = lds + buf * (AR + BR) * kRowBytes + (AR + wn * TJ * 16 + j16) * kRowBytes + 16 * q4;
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
                 u32x4_t a[TI], b[TJ];
@@ -269,78 +202,25 @@ __global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ 
             }
         };
 
-        // ring slot s holds chunk s mod 2; with two LDS buffers, buffer s holds
-        // it while it is multiplied
+        // ring slot s holds chunk s mod 2; LDS buffer s holds it while it is multiplied
         load_chunk(0);
         load_chunk(1);
-        if constexpr (BUFS == 1) {
-            for (int q = 0; q < NQ; q += 2) {
-#pragma unroll
-                for (int s = 0; s < 2; ++s) {
-                    if (q + s >= NQ) break;
-                    store_chunk(s, 0);
-                    __syncthreads();
-                    load_chunk(s);
-                    compute(0);
-                    __syncthreads();
-                }
-            }
-        } else {
+        store_chunk(0, 0);
+        __syncthreads();
+        const int NQP = NQ / 2 * 2;
+        for (int q = 0; q < NQP; q += 2) {
+            load_chunk(0);
+            compute(0);
+            store_chunk(1, 1);
+            __syncthreads();
+            load_chunk(1);
+            compute(1);
             store_chunk(0, 0);
             __syncthreads();
-            const int NQP = NQ / 2 * 2;
-            for (int q = 0; q < NQP; q += 2) {
-                load_chunk(0);
-                compute(0);
-                store_chunk(1, 1);
-                __syncthreads();
-                load_chunk(1);
-                compute(1);
-                store_chunk(0, 0);
-                __syncthreads();
-            }
-            if (NQ & 1) {
-                compute(0);
-                __syncthreads();  // the LDS is rewritten by the next tile
-            }
         }
-
-        if constexpr (SPLIT) {
-            // a result that is not finite may come from an input that is not,
-            // or is too large for the split: the tile once more, each output
-            // as one chain of fp32 FMAs
-            if (tid == 0) redo_s = 0;
-            __syncthreads();
-            bool bad = false;
-#pragma unroll
-            for (int i = 0; i < TI; ++i)
-#pragma unroll
-                for (int j = 0; j < TJ; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
-            if (bad) redo_s = 1;
-            __syncthreads();
-            if (redo_s) {
-#pragma unroll
-                for (int i = 0; i < TI; ++i)
-#pragma unroll
-                    for (int j = 0; j < TJ; ++j)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int rt = (wm * TI + i) * 16 + j16, col = col_base + (wn * TJ + j) * 16 + 4 * q4 + r;
-                            float y = 0.f;
-                            if (col < C_out)
-                                for (int t = 0; t < T; ++t) {
-                                    const int u = nbr_s[rt * T + t];
-                                    if (u < 0) continue;
-                                    const float *xr = reinterpret_cast<const float *>(in) + (int64_t)u * C_in;
-                                    const float *wr = reinterpret_cast<const float *>(wv) + col * K + t * C_in;
-                                    for (int c = 0; c < C_in; ++c) y = fmaf(xr[c], wr[c], y);
-                                }
-                            acc[i][j][r] = y;
-                        }
-            }
-            __syncthreads();  // nbr_s is rewritten by the next tile
+        if (NQ & 1) {
+            compute(0);
+            __syncthreads();  // the LDS is rewritten by the next tile
         }
 
         // register r of lane (j16, q4): row j16, column 4 q4 + r of each tile
@@ -389,7 +269,7 @@ hipError_t go(lattice *L, const void *in, int C_in, const void *w, int C_out, co
     if (grid > tiles) grid = tiles;
     if (grid < 1) grid = 1;
     hipLaunchKernelGGL((k_conv_seg<CM, WM, TI, TJ>), dim3((unsigned)grid), dim3(kThreads), 0, L->stream, in, C_in,
-                       w, C_out, L->T, bias, out, out_bf16 ? 1 : 0, out_vec ? 1 : 0, L->nbr, L->counters, reinterpret_cast<const float *>(L->zero_row));
+                       w, C_out, L->T, bias, out, out_bf16 ? 1 : 0, out_vec ? 1 : 0, L->nbr, L->counters);
     return hipGetLastError();
 }
 
@@ -442,20 +322,8 @@ hipError_t launch_conv_seg(lattice *L, const void *in, lattice_dtype in_dt, int 
     // V = 70 989 35 against 38, so from 400 000 on).
     const bool small = L->max_vertices <= 64 * (int64_t)L->cu_count;
     if (dt == LATTICE_F32) {
-        // fp32 MFMA for small clouds and narrow outputs, whose tiles are bound
-        // by their gathers, the split elsewhere (us, fp32 MFMA -> split):
-        // 64 -> 64 on V = 24 941 / 70 989 / 278 788 28.6 -> 26.9, 60.7 -> 48.3,
-        // 196 -> 160; 96 -> 96 59.7 -> 46.1, 130 -> 94, 528 -> 293; 32 -> 32 11.8 ->
-        // 12.2, 21.9 -> 21.6, 69 -> 53; 8 -> 16 23.9 -> 38.7 on the largest
-        const int width = tile_width(C_out);
-        const bool large = L->max_vertices >= 400000;
         if (small) return by_width<0, 1, 1>(L, in, C_in, w, C_out, bias, out, ob, vec);
-        if (C_in > kSplitMaxC || width == 16 || (width < 64 && !large))
-            return by_width<0, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
-        // 128-row tiles halve the weights' splitting: large lattices, all widths
-        // but 64 (96 -> 96 on V = 278 788 377 -> 293, 64 -> 64 160 -> 164)
-        if (large && width != 64) return by_width<3, 2, 4>(L, in, C_in, w, C_out, bias, out, ob, vec);
-        return by_width<3, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
+        return by_width<0, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
     }
     if (in_dt == LATTICE_F32) {
         if (small) return by_width<1, 1, 1>(L, in, C_in, w, C_out, bias, out, ob, vec);

@@ -193,7 +193,6 @@ hipError_t launch_conv(lattice *L, const void *in, lattice_dtype in_dt, int C_in
                        lattice_dtype dt, const float *bias, void *out, lattice_dtype out_dt);
 
 // conv_seg.hip: any C_in that is a multiple of 4 (16-byte aligned operands)
-constexpr int kSplitMaxC = 256;  // fp32 rows of a zero row's length: what its split path takes
 bool conv_seg_covers(lattice_dtype in_dt, int C_in, lattice_dtype dt);
 hipError_t launch_conv_seg(lattice *L, const void *in, lattice_dtype in_dt, int C_in, const void *w, int C_out,
                            lattice_dtype dt, const float *bias, void *out, lattice_dtype out_dt);

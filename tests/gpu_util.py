@@ -110,3 +110,16 @@ def check_lattice(g: GpuLattice, lat: O.Lattice):
     assert np.array_equal(g.idx, lat.idx)
     assert np.abs(g.bary - lat.bary).max(initial=0.0) <= BARY_ABS
 
+
+
+def fastest_ms(call, n=10):
+    """Device time of the fastest of n calls."""
+    best = float("inf")
+    for _ in range(n):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        call()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best

@@ -14,7 +14,7 @@ import torch
 from datagen.clouds import conv_weight, deform_weights, make_workload, random_cloud, random_rows
 from oracle import lattice_oracle as O
 from tests.gpu_util import (BARY_ABS, REL_BF16, REL_F32, GpuLattice, assert_close_scaled, check_lattice, dev,
-                            to_dev)
+                            fastest_ms, to_dev)
 
 pytestmark = pytest.mark.gpu
 
@@ -824,4 +824,45 @@ def test_conv_f32_extreme_values(C_in, C_out, m):
     ref, scale = O.conv(tiny.astype(np.float64), nbr, W.astype(np.float64))
     assert_close_scaled(g.from_gpu_order(L.conv(g.to_gpu_order(tiny), to_dev(W))), ref, scale, REL_F32, "tiny rows",
                         atol=0.0)
+    L.close()
+
+
+@pytest.mark.parametrize("C_in,C_out,m", [(64, 64, 20000), (128, 128, 20000), (96, 96, 20000), (36, 100, 700)])
+def test_conv_f32_holds_32_bits(C_in, C_out, m):
+    """fp32 rows of 1e-37 to 2e-37 (all normal numbers, whose 24 bits reach
+    down to 2^-147) keep the relative accuracy of ordinary ones: products
+    with weights of +-1 and their sums are fp32, so only a narrower product
+    could lose those bits.  Where the LDS-tiled kernel covers the shape, the
+    default path gives its bits."""
+    w = random_cloud(m, 3, seed=1400, extent=1.0, C=1)
+    L = _lattice(3, 0.2, w.m)
+    g = GpuLattice(L, w.pos, w.feat)
+    lat = O.build(w.pos, 0.2)
+    rng = np.random.default_rng(1401)
+    W = np.sign(rng.standard_normal((C_out, 9, C_in))).astype(np.float32)
+    x = (1e-37 * (1 + rng.random((lat.V, C_in))) * np.sign(rng.standard_normal((lat.V, C_in)))).astype(np.float32)
+    ref, scale = O.conv(x.astype(np.float64), O.neighbors(lat), W.astype(np.float64))
+    assert_close_scaled(g.from_gpu_order(L.conv(g.to_gpu_order(x), to_dev(W))), ref, scale, REL_F32, "rows of 1e-37",
+                        atol=0.0)
+    if C_in % 32 == 0 and C_out % 64 == 0:
+        x, W = g.to_gpu_order(random_rows(lat.V, C_in, seed=1402)), to_dev(conv_weight(C_in, C_out, 3, seed=1403))
+        auto = L.conv(x, W)
+        L.set_conv_path("tiled")
+        assert torch.equal(auto, L.conv(x, W))
+    L.close()
+
+
+@pytest.mark.parametrize("C", [64, 96])
+def test_conv_f32_infinity_costs_nothing(C):
+    """One infinite value among the rows, as an overflowed training step has
+    them, takes the time of ordinary rows (the fastest of several calls each;
+    a factor of 3 is far above their scatter)."""
+    w = random_cloud(40000, 3, seed=1410, extent=1.0, C=1)
+    L = _lattice(3, 0.1, w.m)
+    V = GpuLattice(L, w.pos, w.feat).V
+    L.build_neighbors()
+    x, W = to_dev(random_rows(V, C, seed=1411)), to_dev(conv_weight(C, C, 3, seed=1412))
+    bad = x.clone()
+    bad[V // 2, 3] = float("inf")
+    assert fastest_ms(lambda: L.conv(bad, W)) < 3 * fastest_ms(lambda: L.conv(x, W))
     L.close()
