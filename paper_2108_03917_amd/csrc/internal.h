@@ -59,27 +59,6 @@ __device__ __forceinline__ uint32_t bf16_bits(float f) {
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-
-// An fp32 value as a sum of three bf16: h = bf16(x), m = bf16(x - h), l = x -
-// h - m, which has at most 8 significant bits left, so that h + m + l = x
-// exactly (down to 2^-133).  Of the nine products of two such sums the six
-// largest are taken; the other three are below 2^-23 of the product together,
-// and about 2^-26 of it on average, with random sign: far less than the
-// rounding of fp32 sums.  Two values at a time, packed.  An x
-// that is not finite, or rounds to an infinite h, gives a NaN or an infinity
-// in every product it enters.
-__device__ __forceinline__ void split3(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
-    auto pack = [](float a, float b) {
-        return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
-    };
-    h = pack(x0, x1);
-    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
-    m = pack(r0, r1);
-    l = pack(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
-}
-
 struct lattice_timer {
     double ms = 0.0;    // summed elapsed time of read event pairs
     int64_t count = 0;  // number of read event pairs

@@ -402,3 +402,28 @@ def test_conv_weight_gradient_shapes(d, C_in, C_out, dtype, m):
         inf = np.isinf(ref)
         assert inf.any() and np.array_equal(got[inf], ref[inf])
     L.close()
+
+
+@pytest.mark.parametrize("C_in,C_out,tiny", [(64, 64, "g"), (64, 64, "x"), (36, 100, "both")])
+def test_conv_weight_gradient_small_values(C_in, C_out, tiny):
+    """fp32 gradients or rows of 1e-37 to 2e-37 (both: 1e-21, products of
+    1e-42 below the smallest normal number) keep the accuracy of ordinary
+    ones.  Sums of subnormal products: half a unit of 2^-149 more for each
+    rounding of the sum."""
+    w = random_cloud(300, 3, seed=1420, extent=1.0, C=1)
+    L = _lattice(3, 0.25, w.m)
+    g = GpuLattice(L, w.pos, w.feat)
+    lat = O.build(w.pos, 0.25)
+    nbr = O.neighbors(lat)
+    rng = np.random.default_rng(1421)
+
+    def rows(C, size):
+        return (size * (1 + rng.random((lat.V, C))) * np.sign(rng.standard_normal((lat.V, C)))).astype(np.float32)
+
+    x, go = rows(C_in, {"g": 1, "x": 1e-37, "both": 1e-21}[tiny]), rows(C_out, {"g": 1e-37, "x": 1, "both": 1e-21}[tiny])
+    W = conv_weight(C_in, C_out, 3, seed=1422)
+    got = L.conv_backward(g.to_gpu_order(go), to_dev(W), g.to_gpu_order(x), want_input=False)[1]
+    _, ref, _, _, scale, _ = O.conv_backward(x, nbr, W, go)
+    assert_close_scaled(got.cpu().numpy(), ref, scale, REL_F32, f"weight gradient of small {tiny}",
+                        atol=lat.V * 2.0 ** -150 if tiny == "both" else 0.0)
+    L.close()
