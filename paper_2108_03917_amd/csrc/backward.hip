@@ -453,29 +453,58 @@ __global__ __launch_bounds__(kBlock, 2) void k_conv_wgrad_taps(const void *__res
     auto oc_of = [&](int r) { return o0 + ow + 8 * (r >> 2) + 4 * h + (r & 3); };
     if constexpr (CM == 3) {
         // a sum that is not finite may come from a value too large for the
-        // split, or not finite itself: this wavefront's sums once more, as
-        // chains of fp32 FMAs
+        // split, or not finite itself: this wavefront's sums once more, on
+        // fp32 MFMA (32x32x2: lane l supplies row l / 32 of a pair) with the
+        // operands straight from memory, kRedo pairs and their indices in
+        // flight.  An absent neighbour is left out (0 times 0), not taken as
+        // a zero row, whose product with an infinity would be NaN.  One
+        // infinity, us: V = 10 200 64 -> 64 29 -> 38, 128 -> 128 44 -> 101,
+        // V = 75 500 64 -> 157, 199 -> 559 (every row infinite: 170, 636)
         bool bad = false;
 #pragma unroll
         for (int k = 0; k < kTaps; ++k)
 #pragma unroll
             for (int r = 0; r < 16; ++r) bad |= !(fabsf(acc[k][r]) <= 3.402823466e38f);
         if (__ballot(bad) != 0ull) {
+            constexpr int kRedo = 4;
+            const int oc = o0 + ow + (lane & 31);
+            int32_t u[kRedo][kTaps];
+            auto indices = [&](int64_t v0) {
+#pragma unroll
+                for (int j = 0; j < kRedo; ++j)
+#pragma unroll
+                    for (int k = 0; k < kTaps; ++k) {
+                        const int64_t v = v0 + 2 * j + h;
+                        u[j][k] = v < hi && t0 + k < T ? nbr[v * T + t0 + k] : -1;
+                    }
+            };
 #pragma unroll
             for (int k = 0; k < kTaps; ++k)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    float y = 0.f;
-                    const int oc = oc_of(r);
-                    if (oc < C_out && ic < C_in && t0 + k < T)
-                        for (int64_t v = lo; v < hi; ++v) {
-                            const int u = nbr[v * T + t0 + k];
-                            if (u >= 0)
-                                y = fmaf(reinterpret_cast<const float *>(g)[v * C_out + oc],
-                                         reinterpret_cast<const float *>(x)[(int64_t)u * C_in + ic], y);
-                        }
-                    acc[k][r] = y;
+                for (int r = 0; r < 16; ++r) acc[k][r] = 0.f;
+            indices(lo);
+            for (int64_t v0 = lo; v0 < hi; v0 += 2 * kRedo) {
+                float a[kRedo], b[kRedo][kTaps];
+                bool on[kRedo][kTaps];
+#pragma unroll
+                for (int j = 0; j < kRedo; ++j) {
+                    const int64_t v = v0 + 2 * j + h;
+                    a[j] = v < hi && oc < C_out ? reinterpret_cast<const float *>(g)[v * C_out + oc] : 0.f;
+#pragma unroll
+                    for (int k = 0; k < kTaps; ++k) {
+                        on[j][k] = u[j][k] >= 0;
+                        b[j][k] = on[j][k] && ic < C_in
+                                      ? reinterpret_cast<const float *>(x)[(int64_t)u[j][k] * C_in + ic]
+                                      : 0.f;
+                    }
                 }
+                indices(v0 + 2 * kRedo);
+#pragma unroll
+                for (int j = 0; j < kRedo; ++j)
+#pragma unroll
+                    for (int k = 0; k < kTaps; ++k)
+                        acc[k] = __builtin_amdgcn_mfma_f32_32x32x2f32(on[j][k] ? a[j] : 0.f, b[j][k], acc[k], 0, 0, 0);
+            }
         } else {
 #pragma unroll
             for (int k = 0; k < kTaps; ++k)

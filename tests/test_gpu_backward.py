@@ -15,7 +15,7 @@ import torch
 
 from datagen.clouds import conv_weight, deform_weights, make_workload, random_cloud, random_rows
 from oracle import lattice_oracle as O
-from tests.gpu_util import REL_BF16, REL_F32, GpuLattice, assert_close_scaled, to_dev
+from tests.gpu_util import REL_BF16, REL_F32, GpuLattice, assert_close_scaled, fastest_ms, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -426,4 +426,26 @@ def test_conv_weight_gradient_small_values(C_in, C_out, tiny):
     _, ref, _, _, scale, _ = O.conv_backward(x, nbr, W, go)
     assert_close_scaled(got.cpu().numpy(), ref, scale, REL_F32, f"weight gradient of small {tiny}",
                         atol=lat.V * 2.0 ** -150 if tiny == "both" else 0.0)
+    L.close()
+
+
+@pytest.mark.parametrize("C", [64, 128])
+@pytest.mark.parametrize("where", ["x", "g"])
+def test_conv_weight_gradient_infinity_cost(C, where):
+    """One infinite value among the rows or the gradients, as an overflowed
+    training step has them: the workgroups that meet it sum their chunk once
+    more on fp32 matrix instructions (measured: 1.3 to 3 times an ordinary
+    call; a factor of 5 is above its scatter and below a serial chain's 12 to
+    90)."""
+    w = random_cloud(40000, 3, seed=1430, extent=1.0, C=1)
+    L = _lattice(3, 0.1, w.m)
+    V = GpuLattice(L, w.pos, w.feat).V
+    L.build_neighbors()
+    x, g, W = (to_dev(random_rows(V, C, seed=1431)), to_dev(random_rows(V, C, seed=1432)),
+               to_dev(conv_weight(C, C, 3, seed=1433)))
+    bad = {"x": x.clone(), "g": g.clone()}
+    bad[where][V // 2, 3] = float("inf")
+    xb, gb = (bad["x"], g) if where == "x" else (x, bad["g"])
+    plain = fastest_ms(lambda: L.conv_backward(g, W, x, want_input=False))
+    assert fastest_ms(lambda: L.conv_backward(gb, W, xb, want_input=False)) < 5 * plain
     L.close()
