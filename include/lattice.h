@@ -552,8 +552,10 @@ lattice_status lattice_distribute_pointnet(lattice *L, const float *pos, const f
  *   grad_params  dev fp32 output in the layout of params (per block:
  *                d(gamma or a) [K], d(beta or s) [K], dW [w][K], db [w]);
  *                must not overlap params.
- * The first call grows the lattice's scratch for it (512 bytes per pair and
- * the partial sums).  Returns as the forward, and
+ * The first call grows the lattice's scratch for it (216 bytes per pair and
+ * 256 per vertex of the lattice's bounds, and the partial sums), the first
+ * with groups on a batched lattice also its records (256 bytes per pair).
+ * Returns as the forward, and
  * LATTICE_E_ARG for a missing grad_out or grad_params.
  */
 lattice_status lattice_distribute_pointnet_backward(lattice *L, const float *pos, const float *feat, int f_d,

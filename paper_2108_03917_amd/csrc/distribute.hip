@@ -2106,9 +2106,13 @@ hipError_t launch_distribute_pointnet(lattice *L, const float *pos, const float 
 
 // Scratch of the backward (offsets in bytes, 256-aligned).
 struct DpnLayout {
-    int64_t rec, routed, win, wslot, d3, d2, nrm, rows, gm, parg, pb3, pb2, pb1, r3, r2, r1, rarg, tmp, total;
-    int nwaves_arg, nwaves_route, nwaves, nblk;
+    int64_t routed, win, wslot, d3, d2, nrm, rows, gm, parg, pb3, pb2, pb1, r3, r2, r1, rarg, tmp, total;
+    int nwaves_arg, nwaves_route, nwaves, nblk, nblk1;
 };
+
+// One layout holds either path (batched records apart, see
+// pointnet_backward_record_bytes), so that a lattice's calls of both kinds
+// share one buffer that is allocated once.
 
 static DpnLayout dpn_layout(const lattice *L) {
     auto al = [](int64_t x) { return (x + 255) / 256 * 256; };
@@ -2116,10 +2120,28 @@ static DpnLayout dpn_layout(const lattice *L) {
     l.nwaves_arg = L->cu_count * 4 * kWaves;  // four workgroups of four wavefronts per CU
     l.nwaves_route = L->cu_count * 8 * kWaves;  // without dW3's registers, eight
     l.nwaves = L->cu_count * 4;               // batched passes: four one-wavefront workgroups per CU
-    l.nblk = L->cu_count * 2;                 // the other passes' workgroups: two per CU stay resident
+    l.nblk = L->cu_count * 2;                 // the other passes' workgroups: two per CU stay resident,
+    l.nblk1 = L->cu_count * 3;                // three of pass 1
+    // the partial rows that the two paths write and sum
+    struct Rows {
+        int64_t rows, n;
+    };
+    const Rows arg[2] = {{l.nwaves_arg, kPArg}, {l.nwaves_route, kW3}};
+    const Rows b3[2] = {{l.nwaves, kPB3}, {l.nblk, kQ3}};
+    const Rows b2[2] = {{l.nwaves, kPB2}, {l.nblk, kQ2}};
+    const Rows b1[2] = {{l.nwaves, kPB1}, {l.nblk1, kQ1}};
+    int64_t tmp = 0;  // the sums run one after the other
+    auto partials = [&](const Rows *r) {
+        int64_t most = 0;
+        for (int i = 0; i < 2; ++i) {
+            if (r[i].rows * r[i].n > most) most = r[i].rows * r[i].n;
+            const int64_t t = rowsum::scratch_floats(r[i].rows, r[i].n);
+            if (t > tmp) tmp = t;
+        }
+        return al(most * 4);
+    };
     const int64_t V = L->max_vertices, E = (int64_t)(L->d + 1) * L->max_points;
     int64_t at = 0;
-    l.rec = at;    at += al(E * kRec * 4);
     l.routed = at; at += al(E * 8);
     l.win = at;    at += al(V * kW3 * 4);
     l.wslot = at;  at += al((E + 63) / 64 * 2 * kW3 * 8);
@@ -2128,27 +2150,30 @@ static DpnLayout dpn_layout(const lattice *L) {
     l.nrm = at;    at += al((int64_t)kGnClouds * kNrmRow * 4);
     l.rows = at;   at += al((int64_t)kGnClouds * 8);
     l.gm = at;     at += al((int64_t)kGnClouds * 2 * kW2 * 2 * 4);
-    l.parg = at;   at += al((int64_t)l.nwaves_arg * kPArg * 4);
-    l.pb3 = at;    at += al((int64_t)l.nwaves * kPB3 * 4);
-    l.pb2 = at;    at += al((int64_t)l.nwaves * kPB2 * 4);
-    l.pb1 = at;    at += al((int64_t)l.nwaves * kPB1 * 4);
+    l.parg = at;   at += partials(arg);
+    l.pb3 = at;    at += partials(b3);
+    l.pb2 = at;    at += partials(b2);
+    l.pb1 = at;    at += partials(b1);
     l.r3 = at;     at += al(kPB3 * 4);
     l.r2 = at;     at += al(kPB2 * 4);
     l.r1 = at;     at += al(kPB1 * 4);
     l.rarg = at;   at += al(kPArg * 4);
-    int64_t t = rowsum::scratch_floats(l.nwaves_arg, kPArg);
-    for (int64_t n : {kPB3, kPB2, kPB1})
-        if (rowsum::scratch_floats(l.nwaves, n) > t) t = rowsum::scratch_floats(l.nwaves, n);
-    l.tmp = at;    at += al(t * 4);
+    l.tmp = at;    at += al(tmp * 4);
     l.total = at;
     return l;
 }
 
 int64_t pointnet_backward_scratch_bytes(const lattice *L) { return dpn_layout(L).total; }
 
+// The entries' records, which only the passes of a batched lattice with group
+// normalisation keep.
+int64_t pointnet_backward_record_bytes(const lattice *L, const int *groups) {
+    return groups && L->batched ? (int64_t)(L->d + 1) * L->max_points * kRec * (int64_t)sizeof(float) : 0;
+}
+
 hipError_t launch_distribute_backward(lattice *L, const float *pos, const float *feat, int f_d, const float *params,
                                       const int *groups, float eps, const float *grad_out, float *grad_params,
-                                      void *scratch) {
+                                      void *scratch, float *rec) {
     if (L->m == 0)  // no rows: every gradient is zero (a sum of no rows)
         return rowsum::sum(L->stream, grad_params, 0, pointnet_param_count(L->d + f_d), nullptr, grad_params);
     const DpnLayout l = dpn_layout(L);
@@ -2178,12 +2203,12 @@ hipError_t launch_distribute_backward(lattice *L, const float *pos, const float 
     auto winners = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(g_p), dim3(kBlock), 0, L->stream, L->list, L->lvert, L->vinfo, L->vkeys, batched,
                            pos, feat, L->d, f_d, L->pn_params, L->pn_aff, L->mu, L->counters, L->pn_stats, L->pn_keys,
-                           nullptr, F(l.rec), routed, win, wslot);
+                           nullptr, rec, routed, win, wslot);
         return hipGetLastError();
     };
     auto route = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)(nwaves_a / kWaves)), dim3(kBlock), 0, L->stream, L->vinfo, L->vkeys, batched, L->pn_aff,
-                           F(l.rec), win, wslot, grad_out, L->counters, routed, F(l.parg));
+        hipLaunchKernelGGL(kern, dim3((unsigned)(nwaves_a / kWaves)), dim3(kBlock), 0, L->stream, L->vinfo, L->vkeys,
+                           batched, L->pn_aff, rec, win, wslot, grad_out, L->counters, routed, F(l.parg));
         return hipGetLastError();
     };
     auto reduce = [&](const float *part, int64_t nrows, int64_t n, float *out) {
@@ -2202,22 +2227,21 @@ hipError_t launch_distribute_backward(lattice *L, const float *pos, const float 
                                grad_out, din, dout, L->counters, F(part_off));
             return hipGetLastError();
         };
-        const int nblk1 = L->cu_count * 3;  // pass 1's registers let a CU hold three
         if ((e = winners(k_pointnet<5, false>)) != hipSuccess) return e;
         if ((e = route(k_dpn_argmax<false>)) != hipSuccess) return e;
         if ((e = pass(k_dpn_pass<3>, nullptr, G2, nullptr, F(l.d3), l.pb3, l.nblk)) != hipSuccess) return e;
         if ((e = reduce(F(l.pb3), l.nblk, kQ3, F(l.r3))) != hipSuccess) return e;
         if ((e = pass(k_dpn_pass<2>, F(l.r3), G2, F(l.d3), F(l.d2), l.pb2, l.nblk)) != hipSuccess) return e;
         if ((e = reduce(F(l.pb2), l.nblk, kQ2, F(l.r2))) != hipSuccess) return e;
-        if ((e = pass(k_dpn_pass<1>, F(l.r2), G1, F(l.d2), nullptr, l.pb1, nblk1)) != hipSuccess) return e;
-        const rowsum::Job last[2] = {{F(l.pb1), F(l.r1), nblk1, kQ1}, {F(l.parg), F(l.rarg), nwaves_a, kW3}};
+        if ((e = pass(k_dpn_pass<1>, F(l.r2), G1, F(l.d2), nullptr, l.pb1, l.nblk1)) != hipSuccess) return e;
+        const rowsum::Job last[2] = {{F(l.pb1), F(l.r1), l.nblk1, kQ1}, {F(l.parg), F(l.rarg), nwaves_a, kW3}};
         if ((e = rowsum::sum_all(L->stream, last, 2, F(l.tmp))) != hipSuccess) return e;
         return out(F(l.r3) + 2 * kW2, F(l.rarg));
     }
     auto back = [&](auto kern, int K, const float *din, float *dout, int64_t part_off) {
         const size_t tab = (size_t)kGnClouds * 2 * K * sizeof(float);
         hipLaunchKernelGGL(kern, dim3((unsigned)l.nwaves), dim3(64), tab, L->stream, L->lvert, L->vkeys, G1, G2,
-                           L->pn_params, L->pn_aff, F(l.nrm), F(l.gm), F(l.rec), routed, grad_out, din, dout,
+                           L->pn_params, L->pn_aff, F(l.nrm), F(l.gm), rec, routed, grad_out, din, dout,
                            L->counters, F(part_off));
         return hipGetLastError();
     };

@@ -79,6 +79,7 @@ void free_all(lattice *L) {
     (void)hipFree(L->vslot);
     (void)hipFree(L->dfb);
     (void)hipFree(L->pnb);
+    (void)hipFree(L->pnrec);
     (void)hipFree(L->blk);
     (void)hipFree(L->split);
     (void)hipFree(L->rowmap);
@@ -974,10 +975,13 @@ lattice_status lattice_distribute_pointnet_backward(lattice *L, const float *pos
     if (s) return s;
     if ((s = grow(L, &L->pnb, &L->pnb_bytes, pointnet_backward_scratch_bytes(L), "distribute_pointnet_backward")))
         return s;
+    if ((s = grow(L, &L->pnrec, &L->pnrec_bytes, pointnet_backward_record_bytes(L, groups),
+                  "distribute_pointnet_backward")))
+        return s;
     hipEvent_t t0;
     if ((s = timer_begin(L, LATTICE_STAGE_DISTRIBUTE_BACKWARD, &t0))) return s;
     if ((s = check_launch(L, launch_distribute_backward(L, pos, feat, f_d, params, groups, eps, grad_out, grad_params,
-                                                        L->pnb),
+                                                        L->pnb, reinterpret_cast<float *>(L->pnrec)),
                           "distribute_pointnet_backward")))
         return s;
     return timer_end(L, LATTICE_STAGE_DISTRIBUTE_BACKWARD, t0);

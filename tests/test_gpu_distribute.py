@@ -536,3 +536,41 @@ def test_distribute_pointnet_backward_one_cloud_both_paths(d, m, sigma, f_d, gro
             floor = 1e-5 * max(out[1].norm().item(), 1e-3)
             assert (x - y).norm() <= 1e-2 * y.norm() + floor, (li, n, (x - y).norm().item(), y.norm().item())
     L.close()
+
+
+def test_distribute_pointnet_backward_scratch():
+    """The backward's device memory: an unbatched lattice takes the stated 216
+    bytes per pair and 256 per vertex of its bounds and no entry records, a
+    batched call after it adds the records (256 bytes per pair), and further
+    calls of either kind take nothing."""
+    from paper_2108_03917_amd import Lattice
+
+    m, d = 300000, 3
+    w = random_cloud(m, d, seed=660, extent=1.0, C=1)
+    pos, feat = to_dev(w.pos), to_dev(w.feat)
+    params = Lattice.pack_pointnet(pointnet_gn_weights(d + 1, seed=661)).to("cuda:0")
+    zeros = torch.zeros(m, dtype=torch.int32, device="cuda:0")
+    gp = torch.randn(m, 64, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(662))
+    L = Lattice(d, 0.1, max_points=m)
+    pairs, taken, got = (d + 1) * m, [], []
+
+    def backward(batch):
+        L.splat(pos, None, batch)
+        G = L.slice_backward(gp)
+        L.distribute_pointnet(pos, feat, params, groups="default")
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        a = L.distribute_pointnet_backward(pos, feat, params, G, groups="default")
+        torch.cuda.synchronize()
+        taken.append(free - torch.cuda.mem_get_info()[0])
+        got.append(a)
+
+    for batch in (None, zeros, None, zeros):
+        backward(batch)
+    assert taken[0] <= (216 + 256) * pairs + (96 << 20)      # partial rows: under 96 MB on 256 CUs
+    assert 256 * pairs <= taken[1] <= 256 * pairs + (8 << 20)
+    assert taken[2:] == [0, 0]
+    for a, b in ((0, 2), (1, 3)):       # a new splat's vertex order, and near ties of the maximum with it
+        assert torch.isfinite(got[a]).all()
+        assert (got[a] - got[b]).norm() <= 1e-2 * got[b].norm()
+    L.close()
