@@ -35,6 +35,15 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+typedef u32x4_t u32x4_a8_t __attribute__((aligned(8)));
+
+// One segment from memory.  bf16 rows (and weights) of C_in mod 8 = 4 channels
+// start on 8 bytes, so their 16-byte loads promise no more than that.
+template <typename T, bool A8>
+__device__ __forceinline__ T load_seg(const char *p) {
+    if constexpr (A8) return *reinterpret_cast<const u32x4_a8_t *>(p);
+    else return *reinterpret_cast<const T *>(p);
+}
 
 constexpr int kRowBytes = 144;
 constexpr int kMaxTaps = LATTICE_TAPS(LATTICE_MAX_D);
@@ -120,16 +129,15 @@ __global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ 
                 const int u = nbr_s[(row0 + i * RPP) * T + t];
                 if (in_k && u >= 0) mk |= 1u << i;
                 const int64_t row = u >= 0 ? u : 0;
-                areg[s][i] = *reinterpret_cast<const xseg_t *>(reinterpret_cast<const char *>(in) +
-                                                              (row * C_in + c) * XESZ);
+                areg[s][i] = load_seg<xseg_t, CM == 2>(reinterpret_cast<const char *>(in) + (row * C_in + c) * XESZ);
             }
 #pragma unroll
             for (int i = 0; i < BP; ++i) {
                 const int n = col_base + row0 + i * RPP;
                 const bool ok = in_k && n < C_out && row0 + i * RPP < BN;
                 if (ok) mk |= 1u << (15 + i);
-                breg[s][i] = *reinterpret_cast<const wseg_t *>(reinterpret_cast<const char *>(wv) +
-                                                              ((ok ? n : 0) * K + t * C_in + c) * ESZ);
+                breg[s][i] = load_seg<wseg_t, CM == 2>(reinterpret_cast<const char *>(wv) +
+                                                      ((ok ? n : 0) * K + t * C_in + c) * ESZ);
             }
             mask[s] = mk;
             lc += SEGS;
