@@ -585,6 +585,17 @@ __global__ __launch_bounds__(kBlock) void k_flip_weights(const E *__restrict__ w
 
 }  // namespace
 
+// Whether k_conv_wgrad_taps takes these operands.
+static bool wgrad_vec(const void *g, lattice_dtype g_dt, int C_out, const void *x, lattice_dtype x_dt, int C_in) {
+    return C_out % 4 == 0 && C_in % 4 == 0 && (reinterpret_cast<uintptr_t>(g) & (g_dt == LATTICE_BF16 ? 7 : 15)) == 0 &&
+           (reinterpret_cast<uintptr_t>(x) & (x_dt == LATTICE_BF16 ? 7 : 15)) == 0;
+}
+static bool wgrad_taps(const void *g, lattice_dtype g_dt, int C_out, const void *x, lattice_dtype x_dt, int C_in,
+                       lattice_dtype dt) {
+    return wgrad_vec(g, g_dt, C_out, x, x_dt, C_in) &&
+           (dt == LATTICE_BF16 || (g_dt == LATTICE_F32 && x_dt == LATTICE_F32));
+}
+
 // Number of vertex chunks of the weight gradient, a multiple of 8 (the
 // chunk's workgroups of every tap then share one XCD's L2) and no more than
 // steps of 32 rows in the largest lattice.  One tap per workgroup: about
@@ -592,7 +603,8 @@ __global__ __launch_bounds__(kBlock) void k_flip_weights(const E *__restrict__ w
 // about two per CU, as far as the partials stay within the allocation-free
 // call's workspace (where the first count's do; else that count, so that
 // the same shapes fit it).
-int wgrad_chunks(const lattice *L, int C_in, int C_out) {
+int wgrad_chunks(const lattice *L, const void *g, lattice_dtype g_dt, int C_out, const void *x, lattice_dtype x_dt,
+                 int C_in, lattice_dtype dt) {
     const int64_t tiles = (int64_t)((C_out + kTile - 1) / kTile) * ((C_in + kTile - 1) / kTile);
     const int64_t per = (kWgPerCu * (int64_t)L->cu_count + tiles * L->T - 1) / (tiles * L->T);
     int64_t nch = (per + 7) / 8 * 8;
@@ -604,7 +616,7 @@ int wgrad_chunks(const lattice *L, int C_in, int C_out) {
     int64_t want = 2 * (int64_t)L->cu_count / (tiles * ((L->T + kTaps - 1) / kTaps)) / 8 * 8;
     if (want > fit) want = fit;
     if (want < 8) want = 8;
-    if (nch <= fit && C_in % 4 == 0 && C_out % 4 == 0) nch = want;
+    if (nch <= fit && wgrad_taps(g, g_dt, C_out, x, x_dt, C_in, dt)) nch = want;
     const int64_t steps = (L->max_vertices + kStep - 1) / kStep;
     if (nch > steps) nch = steps;
     if (nch < 1) nch = 1;
@@ -616,12 +628,11 @@ hipError_t launch_conv_wgrad(lattice *L, const void *g, lattice_dtype g_dt, int 
                              lattice_dtype x_dt, int C_in, lattice_dtype dt, int nch, float *partial,
                              float *pbias, float *grad_w, float *grad_bias) {
     const bool gb = g_dt == LATTICE_BF16, xb = x_dt == LATTICE_BF16, rnd = dt == LATTICE_BF16;
-    const bool vec = C_out % 4 == 0 && C_in % 4 == 0 && (reinterpret_cast<uintptr_t>(g) & (gb ? 7 : 15)) == 0 &&
-                     (reinterpret_cast<uintptr_t>(x) & (xb ? 7 : 15)) == 0;
+    const bool vec = wgrad_vec(g, g_dt, C_out, x, x_dt, C_in);
     const dim3 grid((unsigned)nch, (unsigned)L->T,
                     (unsigned)(((C_out + kTile - 1) / kTile) * ((C_in + kTile - 1) / kTile)));
     const int32_t *used = nullptr;  // the counters, where the kernel leaves chunks out
-    if (vec && (rnd || (!gb && !xb))) {
+    if (wgrad_taps(g, g_dt, C_out, x, x_dt, C_in, dt)) {
         used = L->counters;
         const dim3 grid3(grid.x, (unsigned)((L->T + kTaps - 1) / kTaps), grid.z);
         auto go = [&](auto kern) {

@@ -184,7 +184,8 @@ hipError_t launch_splat_backward(lattice *L, const void *grad_values, lattice_dt
                                  const float *vweight, float *grad_feat);
 
 // backward.hip
-int wgrad_chunks(const lattice *L, int C_in, int C_out);
+int wgrad_chunks(const lattice *L, const void *g, lattice_dtype g_dt, int C_out, const void *x, lattice_dtype x_dt,
+                 int C_in, lattice_dtype dt);
 hipError_t launch_conv_wgrad(lattice *L, const void *g, lattice_dtype g_dt, int C_out, const void *x,
                              lattice_dtype x_dt, int C_in, lattice_dtype dt, int nch, float *partial,
                              float *pbias, float *grad_w, float *grad_bias);

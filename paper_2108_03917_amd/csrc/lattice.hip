@@ -643,7 +643,7 @@ lattice_status lattice_conv_backward(lattice *L, const void *grad_out, lattice_d
     if (s) return s;
     if ((s = ensure_neighbors(L))) return s;
     const int T = L->T;
-    const int nch = wgrad_chunks(L, C_in, C_out);
+    const int nch = wgrad_chunks(L, grad_out, g_dtype, C_out, in, in_dtype, C_in, dt);
     if (grad_in) {
         const int64_t esz = dt == LATTICE_BF16 ? 2 : 4;
         if ((s = grow(L, &L->wflip, &L->wflip_bytes, (int64_t)C_out * T * C_in * esz, "conv_backward"))) return s;
@@ -678,7 +678,7 @@ lattice_status lattice_conv_backward_noalloc(lattice *L, const void *grad_out, l
         return LATTICE_E_HIP;
     }
     const int T = L->T;
-    const int nch = wgrad_chunks(L, C_in, C_out);
+    const int nch = wgrad_chunks(L, grad_out, g_dtype, C_out, in, in_dtype, C_in, dt);
     // [flipped weights, padded to 256 bytes][partials of the weight and bias gradients]
     const int64_t flip_bytes = grad_in ? ((int64_t)C_out * T * C_in * (dt == LATTICE_BF16 ? 2 : 4) + 255) / 256 * 256 : 0;
     const int64_t part_bytes =
@@ -804,7 +804,8 @@ static lattice_status resample_backward(lattice *src, lattice *dst, bool up, con
         return LATTICE_E_ARG;
     }
     const int T = dst->T;
-    const int nch = (grad_w || grad_bias) ? wgrad_chunks(dst, C_in, C_out) : 0;
+    const int nch =
+        (grad_w || grad_bias) ? wgrad_chunks(dst, grad_out, g_dtype, C_out, in, in_dtype, C_in, dt) : 0;
     if (grad_in) {
         const int64_t esz = dt == LATTICE_BF16 ? 2 : 4;
         if ((s = grow(src, &src->wflip, &src->wflip_bytes, (int64_t)C_out * T * C_in * esz, what))) return s;
