@@ -294,23 +294,55 @@ struct Row4<3, BF16> {
     __device__ __forceinline__ void zero() { f[0] = f[1] = f[2] = f[3] = 0.f; }
 };
 
-// Chunks that a launch of nch uses for V vertices: at least 2 tiles steps
-// each.  The host knows only the lattice's bound; the kernel and the reduction
-// both take this count, so that a lattice far below its bound does not write
-// and sum partials of a step or two.  A chunk's partial grows with the tiles,
-// and so does the step count at which its traffic is worth a workgroup
-// (V = 5211, T = 9, bf16: 32 -> 32 in chunks of 1, 4 and 8 steps 12.9, 14.0 and
-// 18.5 us; 128 -> 128 26.6, 26.5 and 23.4).
-__device__ __forceinline__ int chunks_used(int64_t V, int nch, int tiles) {
-    const int64_t n = V / (2 * tiles * kTStep) / 8 * 8;
-    return (int)(n < 8 ? (nch < 8 ? nch : 8) : n < nch ? n : (int64_t)nch);
+// Chunks that a launch uses for V vertices, at most `most`.  The host knows
+// only the lattice's bound; the kernel and the reduction both take this count,
+// so that a lattice far below its bound does not write and sum partials of a
+// step or two.  It trades a chunk's serial steps against its partial, which
+// grows with the tiles:
+//   * about `per` steps a chunk, 6 for bf16 over several tiles, else 3, and no
+//     fewer than `low` chunks while there are steps for them, 48 of one tile
+//     and 16 of several.  In multiples of 16: the reduction's four groups load
+//     four partials at a time.
+//   * One tile, or two in bf16: no more than `one`, a workgroup per CU, before
+//     a chunk has 3 (fp32) or 4.5 steps with two per CU: a second workgroup on
+//     some CUs only makes those the last to end.
+// us, T = 9, one-tap kernel | three taps, at least 2 tiles steps a chunk and 8
+// chunks | this rule: bf16 64 -> 64 V = 3 000 17.9 | 14.3 | 14.2, 11 000 19.7 | 24.4
+// | 19.1, 25 000 24.1 | 24.4 | 24.2; 96 -> 96 3 000 16.0 | 20.7 | 16.7, 7 000 20.9 | 23.5
+// | 21.7; fp32 64 -> 64 3 000 20.0 | 18.4 | 16.9, 7 000 23.3 | 25.5 | 22.1; 96 -> 96
+// 2 000 18.9 | 26.6 | 20.1, 3 000 22.1 | 34.5 | 23.3.  Where the one-tap kernel was
+// still better: fp32 16 -> 16 below V = 8 000 by up to 1.6 us (3 000 12.2 | 15.4 |
+// 13.8), bf16 of several tiles up to V = 11 000 by 3 to 8%.
+struct ChunkRule {
+    int most, per, low, one;
+    int64_t two_from;  // steps from which more than `one` are used
+    __device__ __forceinline__ int used(int64_t V) const {
+        const int64_t steps = (V + kTStep - 1) / kTStep;
+        int64_t n = (steps / per + 8) / 16 * 16;
+        const int64_t least = steps < low ? steps : low;
+        if (n < least) n = least;
+        if (n > one && steps < two_from) n = one;
+        if (n > most) n = most;
+        return (int)(n < 1 ? 1 : n);
+    }
+};
+
+ChunkRule chunk_rule(int nch, int tiles, bool bf16) {
+    const bool single = tiles == 1;
+    ChunkRule r;
+    r.most = nch;
+    r.per = bf16 && !single ? 6 : 3;
+    r.low = single ? 48 : 16;
+    r.one = (single || (bf16 && tiles == 2)) && nch >= 32 ? nch / 2 / 8 * 8 : nch;
+    r.two_from = (int64_t)nch * (bf16 ? 9 : 6) / 2;
+    return r;
 }
 
 template <int CM, bool G_BF16, bool X_BF16>
 __global__ __launch_bounds__(kBlock, 2) void k_conv_wgrad_taps(const void *__restrict__ g, int C_out,
                                                                const void *__restrict__ x, int C_in, int T,
                                                                const int32_t *__restrict__ nbr,
-                                                               const int32_t *__restrict__ counters, int max_chunks,
+                                                               const int32_t *__restrict__ counters, ChunkRule rule,
                                                                float *__restrict__ partial,
                                                                float *__restrict__ pbias) {
     constexpr int Z = CM == 3 ? 3 : 1;               // planes
@@ -319,14 +351,17 @@ __global__ __launch_bounds__(kBlock, 2) void k_conv_wgrad_taps(const void *__res
     __shared__ __attribute__((aligned(16))) char xs[kTaps * Z * PLANE];
     __shared__ float bred[kBlock / 16][kTile];
 
+    // the workgroups that are used come first in the order of the grid, so
+    // that they spread evenly over the CUs
     const int64_t V = counters[CNT_V];
-    const int chunk = blockIdx.x;
-    const int nch = chunks_used(V, max_chunks, gridDim.z);
-    if (chunk >= nch) return;
-    const int t0 = blockIdx.y * kTaps;
+    const int nch = rule.used(V), groups = gridDim.y;
+    const int id = blockIdx.x + gridDim.x * (blockIdx.y + groups * blockIdx.z);
+    if (id >= nch * groups * (int)gridDim.z) return;
+    const int chunk = id % nch, tile = id / nch / groups;
+    const int t0 = id / nch % groups * kTaps;
     const int tiles_i = (C_in + kTile - 1) / kTile;
-    const int o0 = (blockIdx.z / tiles_i) * kTile;
-    const int i0 = (blockIdx.z % tiles_i) * kTile;
+    const int o0 = tile / tiles_i * kTile;
+    const int i0 = tile % tiles_i * kTile;
     const int64_t lo = V * chunk / nch;
     const int64_t hi = V * (chunk + 1) / nch;
     const bool do_bias = pbias != nullptr && t0 == 0 && i0 == 0;
@@ -539,23 +574,26 @@ __global__ __launch_bounds__(kBlock, 2) void k_conv_wgrad_taps(const void *__res
 // the four group sums are added in group order.
 constexpr int kRedCols = 64;
 __global__ __launch_bounds__(kBlock) void k_wgrad_reduce(const float *__restrict__ part,
-                                                         const int32_t *__restrict__ counters, int nch, int tiles,
+                                                         const int32_t *__restrict__ counters, ChunkRule rule,
                                                          int64_t n, float *__restrict__ out) {
     __shared__ float red[kBlock / kRedCols][kRedCols];
-    if (counters) nch = chunks_used(counters[CNT_V], nch, tiles);
+    const int nch = counters ? rule.used(counters[CNT_V]) : rule.most;
     const int g = threadIdx.x / kRedCols;
     const int64_t j = (int64_t)blockIdx.x * kRedCols + (threadIdx.x % kRedCols);
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
     if (j < n) {
         constexpr int G = kBlock / kRedCols;
-        int c = g;
-        for (; c + 3 * G < nch; c += 4 * G) {
-            s0 += part[(int64_t)c * n + j];
-            s1 += part[(int64_t)(c + G) * n + j];
-            s2 += part[(int64_t)(c + 2 * G) * n + j];
-            s3 += part[(int64_t)(c + 3 * G) * n + j];
+        // (past the last chunk the group's first one is loaded, and not added)
+        for (int c = g; c < nch; c += 4 * G) {
+            const int c1 = c + G, c2 = c + 2 * G, c3 = c + 3 * G;
+            const float x0 = part[(int64_t)c * n + j], x1 = part[(int64_t)(c1 < nch ? c1 : c) * n + j];
+            const float x2 = part[(int64_t)(c2 < nch ? c2 : c) * n + j];
+            const float x3 = part[(int64_t)(c3 < nch ? c3 : c) * n + j];
+            s0 += x0;
+            s1 += c1 < nch ? x1 : 0.f;
+            s2 += c2 < nch ? x2 : 0.f;
+            s3 += c3 < nch ? x3 : 0.f;
         }
-        for (; c < nch; c += G) s0 += part[(int64_t)c * n + j];
     }
     red[g][threadIdx.x % kRedCols] = (s0 + s1) + (s2 + s3);
     __syncthreads();
@@ -612,8 +650,11 @@ int wgrad_chunks(const lattice *L, const void *g, lattice_dtype g_dt, int C_out,
     const int64_t room = LATTICE_NOALLOC_WORKSPACE_BYTES - (n * 4 + 255) / 256 * 256;
     const int64_t fit = room / ((n + C_out) * 4) / 8 * 8;
     // rounded down: 528 workgroups over 512 places took a second round (fp32
-    // 32 -> 32 on V = 278 788 246 us against 167 for 64 -> 64)
-    int64_t want = 2 * (int64_t)L->cu_count / (tiles * ((L->T + kTaps - 1) / kTaps)) / 8 * 8;
+    // 32 -> 32 on V = 278 788 246 us against 167 for 64 -> 64); many chunks to
+    // the reduction's 16 (fp32 64 -> 64 on V = 40 000 in 168 and 160 chunks: 40.3
+    // and 38.2)
+    int64_t want = 2 * (int64_t)L->cu_count / (tiles * ((L->T + kTaps - 1) / kTaps));
+    want = want >= 64 ? want / 16 * 16 : want / 8 * 8;
     if (want > fit) want = fit;
     if (want < 8) want = 8;
     if (nch <= fit && wgrad_taps(g, g_dt, C_out, x, x_dt, C_in, dt)) nch = want;
@@ -631,13 +672,14 @@ hipError_t launch_conv_wgrad(lattice *L, const void *g, lattice_dtype g_dt, int 
     const bool vec = wgrad_vec(g, g_dt, C_out, x, x_dt, C_in);
     const dim3 grid((unsigned)nch, (unsigned)L->T,
                     (unsigned)(((C_out + kTile - 1) / kTile) * ((C_in + kTile - 1) / kTile)));
+    const ChunkRule rule = chunk_rule(nch, (int)grid.z, rnd);
     const int32_t *used = nullptr;  // the counters, where the kernel leaves chunks out
     if (wgrad_taps(g, g_dt, C_out, x, x_dt, C_in, dt)) {
         used = L->counters;
         const dim3 grid3(grid.x, (unsigned)((L->T + kTaps - 1) / kTaps), grid.z);
         auto go = [&](auto kern) {
             hipLaunchKernelGGL(kern, grid3, dim3(kBlock), 0, L->stream, g, C_out, x, C_in, L->T, L->nbr, L->counters,
-                               nch, partial, grad_bias ? pbias : nullptr);
+                               rule, partial, grad_bias ? pbias : nullptr);
         };
         if (!rnd) go(k_conv_wgrad_taps<3, false, false>);
         else if (gb && xb) go(k_conv_wgrad_taps<1, true, true>);
@@ -674,13 +716,12 @@ hipError_t launch_conv_wgrad(lattice *L, const void *g, lattice_dtype g_dt, int 
     if (grad_w) {
         const int64_t n = (int64_t)C_out * L->T * C_in;
         hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((n + kRedCols - 1) / kRedCols)), dim3(kBlock), 0,
-                           L->stream, partial, used, nch, (int)grid.z, n, grad_w);
+                           L->stream, partial, used, rule, n, grad_w);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (grad_bias) {
         hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((C_out + kRedCols - 1) / kRedCols)), dim3(kBlock), 0,
-                           L->stream, pbias, used, nch, (int)grid.z, (int64_t)C_out,
-                           grad_bias);
+                           L->stream, pbias, used, rule, (int64_t)C_out, grad_bias);
         e = hipGetLastError();
     }
     return e;

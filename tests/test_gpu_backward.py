@@ -449,3 +449,31 @@ def test_conv_weight_gradient_infinity_cost(C, where):
     plain = fastest_ms(lambda: L.conv_backward(g, W, x, want_input=False))
     assert fastest_ms(lambda: L.conv_backward(gb, W, xb, want_input=False)) < 5 * plain
     L.close()
+
+
+@pytest.mark.parametrize("C_in,C_out", [(64, 64), (96, 96), (128, 64)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [4, 36, 500, 1600, 6000, 15000, 30000])
+def test_conv_weight_gradient_chunks(C_in, C_out, dtype, V):
+    """Every side of the chunk rule (fewer steps than chunks, the least
+    chunks, a workgroup per CU, two), with a bound far above V: points far
+    apart, about V vertices of a lattice made for 60 000 points."""
+    w = random_cloud(V // 4, 3, seed=1440, extent=1.0, C=1)
+    L = _lattice(3, 0.01, 60000)
+    g = GpuLattice(L, w.pos, None)
+    rng = np.random.default_rng(1441)
+    x = rng.standard_normal((g.V, C_in)).astype(np.float32)
+    go = rng.standard_normal((g.V, C_out)).astype(np.float32)
+    wd = to_dev(conv_weight(C_in, C_out, 3, seed=1442))
+    if dtype == "bf16":
+        x, go, wd = O.round_bf16(x), O.round_bf16(go), L.weights_to_bf16(wd)
+    nbr = L.neighbors().cpu().numpy()          # rows stay in the lattice's own order
+    _, gw, gb = L.conv_backward(to_dev(go), wd, to_dev(x), dtype=dtype, want_input=False, want_bias=True)
+    for t in range(9):
+        on = nbr[:, t] >= 0
+        gt, xt = go[on].astype(np.float64), x[nbr[on, t]].astype(np.float64)
+        assert_close_scaled(gw[:, t].cpu().numpy(), gt.T @ xt, np.abs(gt).T @ np.abs(xt), REL_F32,
+                            f"weight gradient of {g.V} vertices, tap {t}")
+    assert_close_scaled(gb.cpu().numpy(), go.astype(np.float64).sum(0), np.abs(go).astype(np.float64).sum(0), REL_F32,
+                        f"bias gradient of {g.V} vertices")
+    L.close()
