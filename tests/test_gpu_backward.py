@@ -254,6 +254,38 @@ def test_deform_slice_backward_long_pair_lists(C, n_cls, bf16):
             assert_close_scaled(gbc.cpu().numpy(), rbc, sbc, REL_F32, tag + " b_cls")
 
 
+@pytest.mark.parametrize("d,C", [(3, 8), (3, 20), (3, 32), (3, 36), (4, 36), (3, 100), (3, 256), (4, 256), (3, 260)])
+@pytest.mark.parametrize("grad_dtype", ["f32", "bf16"])
+def test_deform_slice_backward_vertex_gradient(d, C, grad_dtype):
+    """The vertex gradient's gather at every group width (4 to 64 lanes a
+    list), full and with idle lanes, and past the last one, in both storage
+    types: split lists beside short ones against the oracle (bf16: one
+    rounding more), and an output off its 16- or 8-byte boundary, which takes
+    the wavefront-per-list kernel and its order of sums."""
+    pos = _clustered(74, 3000, 1500)
+    if d == 4:
+        pos = np.concatenate([pos, 0.5 * (np.arange(pos.shape[0]) % 2)[:, None].astype(np.float32)], axis=1)
+    L, g, lat = _setup(d, 0, 0.1, 0, pos=pos)
+    counts = np.bincount(lat.idx.reshape(-1), minlength=lat.V)
+    assert (counts > 32).sum() >= 3 and (counts <= 32).sum() > 100
+    y = random_rows(lat.V, C, seed=75 + C)
+    dw = deform_weights(C, 1, seed=76 + C)
+    G = random_rows(pos.shape[0], C, seed=77 + C)
+    (rX, *_), (sX, *_) = O.deform_slice_backward(lat.idx, lat.bary, y, dw.w_delta, dw.b_delta, G, lat.V)
+    tol = REL_F32 * sX + (2.0 ** -8 * np.abs(rX) if grad_dtype == "bf16" else 0.0)
+    yd, wd, Gd = g.to_gpu_order(y), to_dev(dw.w_delta), to_dev(G)
+    gv = L.deform_slice_backward(yd, wd, dw.b_delta, Gd, grad_dtype=grad_dtype)[0]
+    assert_close_scaled(g.from_gpu_order(gv.float()), rX, tol, 1.0, f"vertex gradient d={d} C={C} {grad_dtype}")
+    flat = torch.empty(gv.numel() + 1, dtype=gv.dtype, device="cuda:0")
+    off = flat[1:].view(gv.shape)
+    st = L._lib.lattice_deform_slice_backward(
+        L._h, yd.data_ptr(), 0, C, wd.data_ptr(), float(dw.b_delta), None, 0, Gd.data_ptr(), off.data_ptr(),
+        1 if grad_dtype == "bf16" else 0, None, None, None, None)
+    assert st == 0
+    assert_close_scaled(g.from_gpu_order(off.float()), rX, tol, 1.0, f"unaligned vertex gradient d={d} C={C}")
+    L.close()
+
+
 @pytest.mark.parametrize("n_cls", [0, 20])
 def test_deform_slice_backward_empty_cloud(n_cls):
     """An empty cloud after a non-empty one on the same lattice: no pairs, so
