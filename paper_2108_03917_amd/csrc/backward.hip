@@ -237,6 +237,11 @@ typedef u32x4_t u32x4_a4_t __attribute__((aligned(4)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
+// Two values rounded to bf16 (to nearest even), the first in the low half.
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+}
+
 // 2^24 x of an fp32 value as a sum of three bf16: h = bf16(y), m = bf16(y -
 // h), l = y - h - m for y = 2^24 x, which has at most 8 significant bits left,
 // so that h + m + l = y exactly.  The scale is there because the matrix cores
@@ -250,39 +255,37 @@ typedef float f32x2_t __attribute__((ext_vector_type(2)));
 // more, gives a NaN or an infinity in every product it enters.
 constexpr float kSplitScale = 16777216.f, kSplitBack = 3.552713678800501e-15f;  // 2^24, 2^-48
 __device__ __forceinline__ void split3(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
-    auto pack = [](float a, float b) {
-        return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
-    };
     const float y0 = kSplitScale * x0, y1 = kSplitScale * x1;
-    h = pack(y0, y1);
+    h = pack_bf16(y0, y1);
     const float r0 = y0 - __uint_as_float(h << 16), r1 = y1 - __uint_as_float(h & 0xffff0000u);
-    m = pack(r0, r1);
-    l = pack(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
+    m = pack_bf16(r0, r1);
+    l = pack_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
 }
 
 constexpr int kTStep = 32;   // vertices per step (two MFMA K-steps of 16)
 constexpr int kTRow = 68;    // LDS bytes per channel row: 32 bf16 + 4 bytes of padding
 constexpr int kTaps = 3;     // taps per workgroup
 
-// Four consecutive channels of a row as the products take them: bf16 bits
-// (rounded to nearest even from fp32 storage), or fp32.
-template <int CM, bool BF16>
-struct Row4;
+// Four consecutive channels of a row as loaded: bf16 bits, or fp32, which
+// goes through the split or is rounded to bf16 (to nearest even) only when its
+// step is staged: a conversion here would wait for the load.
 template <bool BF16>
-struct Row4<1, BF16> {
+struct Row4;
+template <>
+struct Row4<true> {
     uint2 u;
     __device__ __forceinline__ void load(const void *base, int64_t row, int C, int c) {
-        if (BF16) {
-            u = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(base) + row * C + c);
-        } else {
-            const float4 f = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(base) + row * C + c);
-            u = make_uint2(bf16_bits(f.x) | (bf16_bits(f.y) << 16), bf16_bits(f.z) | (bf16_bits(f.w) << 16));
-        }
+        u = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(base) + row * C + c);
     }
     __device__ __forceinline__ void zero() { u = make_uint2(0u, 0u); }
+    // channel e of this row and of the next, the bf16 pair of one LDS word
+    __device__ __forceinline__ uint32_t pair(const Row4 &next, int e) const {
+        const int sh = (e & 1) * 16;
+        return (((e < 2 ? u.x : u.y) >> sh) & 0xffffu) | (((e < 2 ? next.u.x : next.u.y) >> sh) << 16);
+    }
 };
-template <bool BF16>
-struct Row4<3, BF16> {
+template <>
+struct Row4<false> {
     float f[4];
     __device__ __forceinline__ void load(const void *base, int64_t row, int C, int c) {
         const float4 t = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(base) + row * C + c);
@@ -292,6 +295,7 @@ struct Row4<3, BF16> {
         f[3] = t.w;
     }
     __device__ __forceinline__ void zero() { f[0] = f[1] = f[2] = f[3] = 0.f; }
+    __device__ __forceinline__ uint32_t pair(const Row4 &next, int e) const { return pack_bf16(f[e], next.f[e]); }
 };
 
 // Chunks that a launch uses for V vertices, at most `most`.  The host knows
@@ -385,8 +389,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_conv_wgrad_taps(const void *__res
     float bsum[4] = {0.f, 0.f, 0.f, 0.f};
 
     // the rows of two steps (slot: step mod 2), and the next step's indices
-    Row4<CM, G_BF16> ga[2][2];
-    Row4<CM, X_BF16> xa[2][kTaps][2];
+    Row4<G_BF16> ga[2][2];
+    Row4<X_BF16> xa[2][kTaps][2];
     int32_t un[kTaps][2];
     auto load_index = [&](int64_t k0) {
 #pragma unroll
@@ -434,9 +438,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_conv_wgrad_taps(const void *__res
                 *reinterpret_cast<uint32_t *>(at + PLANE) = mm;
                 *reinterpret_cast<uint32_t *>(at + 2 * PLANE) = ll;
             } else {
-                const int sh = (e & 1) * 16;
-                *reinterpret_cast<uint32_t *>(at) = (((e < 2 ? r0.u.x : r0.u.y) >> sh) & 0xffffu) |
-                                                    (((e < 2 ? r1.u.x : r1.u.y) >> sh) << 16);
+                *reinterpret_cast<uint32_t *>(at) = r0.pair(r1, e);
             }
         }
     };
