@@ -234,13 +234,6 @@ __global__ __launch_bounds__(kBlock) void k_conv_wgrad(const void *__restrict__ 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef u32x4_t u32x4_a4_t __attribute__((aligned(4)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-
-// Two values rounded to bf16 (to nearest even), the first in the low half.
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
-}
 
 // 2^24 x of an fp32 value as a sum of three bf16: h = bf16(y), m = bf16(y -
 // h), l = y - h - m for y = 2^24 x, which has at most 8 significant bits left,

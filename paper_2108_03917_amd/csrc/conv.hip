@@ -1393,10 +1393,12 @@ hipError_t dispatch_out(lattice *L, const void *in, lattice_dtype in_dt, int C_i
     // one but 64 -> a multiple of 128 with 9 taps, where the resident weight
     // slice is a little faster (64 -> 256, us, V = 24 941 / 70 989 / 278 788:
     // 22.6 / 57.8 / 187 against 26.7 / 56.1 / 198; elsewhere e.g. 128 -> 64 on
-    // V = 70 989 41 against 27, fp32 rows 64 -> 64 47 against 31), the fp32
-    // ones the LDS-tiled kernel is not built for, and fp32 -> 64 channels on
-    // small clouds, whose 64-row tiles leave CUs idle (64 -> 64 on V = 5 211:
-    // 17.0 against 12.9; larger: 58.6 against 60.2)
+    // V = 70 989 41 against 27, fp32 rows 64 -> 64 47 against 24 and 128 -> 64 on
+    // V = 294 000 183 against 166; the most it loses is bf16 rows 128 -> 64 on
+    // V = 182 000, 62 against 68), the fp32 ones the LDS-tiled kernel is not
+    // built for, and fp32 -> 64 channels on small clouds, whose 64-row tiles
+    // leave CUs idle (64 -> 64 on V = 5 211: 17.0 against 12.9; larger: 58.6
+    // against 60.2)
     const bool seg = aligned && conv_seg_covers(in_dt, C_in, dt);
     const lattice_dtype out_dt = OUT_BF16 ? LATTICE_BF16 : LATTICE_F32;
     const bool small = L->max_vertices <= 64 * (int64_t)L->cu_count;

@@ -156,8 +156,8 @@ __global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ 
                 wseg_t y;
                 if constexpr (CM == 1) {
                     const xseg_t x = areg[s][i];
-                    y[0] = bf16_bits(__uint_as_float(x[0])) | (bf16_bits(__uint_as_float(x[1])) << 16);
-                    y[1] = bf16_bits(__uint_as_float(x[2])) | (bf16_bits(__uint_as_float(x[3])) << 16);
+                    y[0] = pack_bf16(__uint_as_float(x[0]), __uint_as_float(x[1]));
+                    y[1] = pack_bf16(__uint_as_float(x[2]), __uint_as_float(x[3]));
                 } else {
                     y = areg[s][i];
                     if constexpr (CM == 2) y = hi ? u32x4_t{y[2], y[3], 0u, 0u} : y;

@@ -59,6 +59,14 @@ __device__ __forceinline__ uint32_t bf16_bits(float f) {
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+// Two values rounded to bf16 (to nearest even), the first in the low half, in
+// one instruction.
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+}
+
 struct lattice_timer {
     double ms = 0.0;    // summed elapsed time of read event pairs
     int64_t count = 0;  // number of read event pairs
