@@ -76,7 +76,9 @@ typedef enum {
 } lattice_status;
 
 typedef enum {
-    LATTICE_F32 = 0,  /* fp32 inputs and weights, fp32 accumulation (fp32 MFMA or FMA) */
+    LATTICE_F32 = 0,  /* fp32 inputs and weights, products and accumulation in fp32 (fp32 MFMA or FMA), or
+                       * products as six of the nine of exact three-term bf16 splits: what is left out is
+                       * below 2^-23 of a product, and the error against 64 bits no larger */
     LATTICE_BF16 = 1  /* inputs rounded to bf16 (nearest even), bf16 weights, fp32 accumulation on MFMA */
 } lattice_dtype;
 
@@ -175,7 +177,8 @@ lattice_status lattice_build_neighbors(lattice *L);
  *              bf16 (raw 16-bit patterns) for LATTICE_BF16 (see
  *              lattice_weights_to_bf16).
  *   C_out      output channels, 1..1024.
- *   dt         compute type.  LATTICE_F32: fp32 products and sums.
+ *   dt         compute type.  LATTICE_F32: fp32 products (or split ones, see
+ *              lattice_dtype) and fp32 sums.
  *              LATTICE_BF16: inputs rounded to bf16 (nearest even; a no-op
  *              for bf16-stored input), exact products, fp32 sums.
  *   bias       dev [C_out] fp32 or NULL.

@@ -1395,16 +1395,22 @@ hipError_t dispatch_out(lattice *L, const void *in, lattice_dtype in_dt, int C_i
     // 22.6 / 57.8 / 187 against 26.7 / 56.1 / 198; elsewhere e.g. 128 -> 64 on
     // V = 70 989 41 against 27, fp32 rows 64 -> 64 47 against 24 and 128 -> 64 on
     // V = 294 000 183 against 166; the most it loses is bf16 rows 128 -> 64 on
-    // V = 182 000, 62 against 68), the fp32 ones the LDS-tiled kernel is not
-    // built for, and fp32 -> 64 channels on small clouds, whose 64-row tiles
-    // leave CUs idle (64 -> 64 on V = 5 211: 17.0 against 12.9; larger: 58.6
-    // against 60.2)
+    // V = 182 000, 62 against 68).
+    // Of the fp32 ones it takes those that the LDS-tiled kernel is not built
+    // for; on small clouds, whose 64-row tiles leave CUs idle, 64 output
+    // channels (64 -> 64 on V = 5 211: 17.0 against 12.9); and all of a large
+    // lattice, where its split into bf16 products pays (64 -> 64, 128 -> 128,
+    // 256 -> 256 on V = 263 000 206 against 162, 669 against 465, 2609 against
+    // 1711; on V = 32 100 of a bound of 415 556 30.8 against 29.3, 92 against 82,
+    // 319 against 209).  In between the tiled kernel stays: with a bound of
+    // 80 000 and V = 10 200 the split took 22.5 against 18.6 and 63 against 50,
+    // with 160 000 and V = 69 800 49 against 58 and 183 against 193.
     const bool seg = aligned && conv_seg_covers(in_dt, C_in, dt);
     const lattice_dtype out_dt = OUT_BF16 ? LATTICE_BF16 : LATTICE_F32;
     const bool small = L->max_vertices <= 64 * (int64_t)L->cu_count;
     if (seg && path == LATTICE_CONV_AUTO) {
         const bool ws = in_bf16 && L->T == 9 && C_in == 64 && C_out % 128 == 0;
-        const bool tiled = C_in % 32 == 0 && C_out % 64 == 0 && !(small && C_out == 64);
+        const bool tiled = C_in % 32 == 0 && C_out % 64 == 0 && (small ? C_out != 64 : L->max_vertices < kConvLarge);
         if (bf16 ? !ws : !tiled) return launch_conv_seg(L, in, in_dt, C_in, w, C_out, dt, bias, out, out_dt);
     }
     if (aligned && path != LATTICE_CONV_TILED) {

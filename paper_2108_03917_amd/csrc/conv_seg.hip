@@ -19,12 +19,21 @@
 // weights as the A operand, so that a lane ends up with four consecutive
 // output channels of one row and stores them at once.
 //
+// fp32 products run on the bf16 matrix cores, 15 times as fast, as six
+// products of three-term splits (see split3), which keep every bit of the
+// values; their error against 64 bits is a little below fp32 MFMA's (64 -> 64
+// 3e-7 against 4e-7, 128 -> 128 4e-7 against 5e-7: fewer roundings of the
+// running sum).  A tile with a result that is not finite is computed once
+// more on fp32 MFMA: with one infinity among the rows 96 -> 96 takes 40 -> 73 us
+// on V = 10 200, 123 -> 147 on V = 75 500.
+//
 // What bounds it: bf16, the gathers and the weight rows through L2 (each tile
-// re-reads W); fp32, the matrix cores (90 of 154 TFLOP/s).  Against the
-// element-wise kernel that took these shapes before (us, before -> now):
-// V = 278 788, 9 taps: bf16 32 -> 32 115 -> 30, 96 -> 96 546 -> 109, 100 -> 100
-// 583 -> 159, fp32 96 -> 96 963 -> 522, 8 -> 16 90 -> 24; V = 24 941: fp32
-// 96 -> 96 114 -> 56.
+// re-reads W); the split, its own vector instructions (6.5 a value and stage)
+// and LDS; fp32 MFMA, the matrix cores (90 of 154 TFLOP/s).  Against the
+// element-wise kernel that took these shapes before (us, before -> now), 9
+// taps: V = 278 788 bf16 32 -> 32 115 -> 30, 96 -> 96 546 -> 109, 100 -> 100
+// 583 -> 159, fp32 8 -> 16 90 -> 24; V = 263 000 fp32 96 -> 96 1031 -> 297,
+// 100 -> 100 1106 -> 374; V = 32 000 fp32 96 -> 96 118 -> 48.
 #include <type_traits>
 
 #include "internal.h"
@@ -45,35 +54,47 @@ __device__ __forceinline__ T load_seg(const char *p) {
     else return *reinterpret_cast<const T *>(p);
 }
 
-constexpr int kRowBytes = 144;
 constexpr int kMaxTaps = LATTICE_TAPS(LATTICE_MAX_D);
 constexpr int kThreads = 256;
 
-// CM 0: fp32 rows and weights, fp32 MFMA; CM 1: fp32 rows rounded to bf16
+// CM 0: fp32 rows and weights, fp32 MFMA; CM 3: the same on bf16 MFMA, see
+// split3; CM 1: fp32 rows rounded to bf16
 // while staging, bf16 weights; CM 2: bf16 rows and weights.  The four
 // wavefronts are WM x (4 / WM), each TI x TJ tiles of 16 x 16.
 template <int CM, int WM, int TI, int TJ>
-__global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ in, int C_in,
+__global__ __launch_bounds__(kThreads, CM != 3 ? 1 : TI * TJ > 6 ? 2 : TI * TJ == 6 ? 3 : 4) void k_conv_seg(const void *__restrict__ in, int C_in,
                                                        const void *__restrict__ wv, int C_out, int T,
                                                        const float *__restrict__ bias, void *__restrict__ out,
                                                        int out_bf16, int out_vec, const int32_t *__restrict__ nbr,
-                                                       const int32_t *__restrict__ counters) {
+                                                       const int32_t *__restrict__ counters,
+                                                       const float *__restrict__ zero_row) {
     constexpr int WN = 4 / WM;
     constexpr int BM = WM * TI * 16, BN = WN * TJ * 16;
     constexpr int SE = CM == 2 ? 8 : 4;               // channels per segment
-    constexpr int ESZ = CM == 0 ? 4 : 2;              // operand element in LDS
+    constexpr bool SPLIT = CM == 3;
+    constexpr int ESZ = CM == 0 || SPLIT ? 4 : 2;     // weight element (and staged element, unless split)
     constexpr int SB = SE * ESZ;                      // LDS (and weight) bytes per segment
     constexpr int XESZ = CM == 2 ? 2 : 4;             // stored input element: 16 bytes of input per segment
     constexpr int SEGS = 128 / SB;                    // segments per row and chunk
     constexpr int RPP = kThreads / SEGS;              // rows per pass
     constexpr int AP = (BM + RPP - 1) / RPP, BP = (BN + RPP - 1) / RPP;
     constexpr int AR = AP * RPP, BR = BP * RPP;       // LDS rows (whole passes)
+    // One LDS row: 128 bytes and 16 of padding (16 rows read 16 bytes each on
+    // 64 different banks), or three planes of 64 bytes without: four rows'
+    // 8-byte writes then fill the 64 banks, and 16-byte chunk c of row r sits at
+    // c ^ (r / 4 % 4), which spreads the reads of 16 rows the same way (padded
+    // rows had 2-way conflicts on the writes, half of the LDS time)
+    constexpr int kRowBytes = SPLIT ? 3 * 64 : 128 + 16;
     constexpr int P = 2;                              // chunks in the register ring
     typedef u32x4_t xseg_t;
     typedef typename std::conditional<SB == 16, u32x4_t, u32x2_t>::type wseg_t;
 
-    __shared__ __attribute__((aligned(16))) char lds[2 * (AR + BR) * kRowBytes];
+    // LDS buffers: the split's planes take one (two to four workgroups per CU
+    // hide its second barrier), the others two
+    constexpr int BUFS = SPLIT ? 1 : 2;
+    __shared__ __attribute__((aligned(16))) char lds[BUFS * (AR + BR) * kRowBytes];
     __shared__ int32_t nbr_s[AR * kMaxTaps];
+    __shared__ int redo_s;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
@@ -129,7 +150,11 @@ __global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ 
                 const int u = nbr_s[(row0 + i * RPP) * T + t];
                 if (in_k && u >= 0) mk |= 1u << i;
                 const int64_t row = u >= 0 ? u : 0;
-                areg[s][i] = load_seg<xseg_t, CM == 2>(reinterpret_cast<const char *>(in) + (row * C_in + c) * XESZ);
+                // (SPLIT reads zeros there instead: every select saved is an
+                // issue slot, which is what it is short of)
+                const char *at = reinterpret_cast<const char *>(in) + (row * C_in + c) * XESZ;
+                if (SPLIT) at = in_k && u >= 0 ? at : reinterpret_cast<const char *>(zero_row);
+                areg[s][i] = load_seg<xseg_t, CM == 2>(at);
             }
 #pragma unroll
             for (int i = 0; i < BP; ++i) {
@@ -144,6 +169,21 @@ __global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ 
             while (lc >= spr) {
                 lc -= spr;
                 ++lt;
+            }
+        };
+        // one staged segment: at its place in the row, or split over the planes
+        auto put = [&](char *row, wseg_t y) {
+            if constexpr (SPLIT) {
+                uint32_t h[2], m[2], l[2];
+                split3(__uint_as_float(y[0]), __uint_as_float(y[1]), h[0], m[0], l[0]);
+                split3(__uint_as_float(y[2]), __uint_as_float(y[3]), h[1], m[1], l[1]);
+                // (rows a multiple of 32 apart: r / 4 % 4 is row0's for every pass)
+                char *at = row + 16 * ((seg >> 1) ^ ((row0 >> 2) & 3)) + 8 * (seg & 1);
+                *reinterpret_cast<u32x2_t *>(at) = u32x2_t{h[0], h[1]};
+                *reinterpret_cast<u32x2_t *>(at + 64) = u32x2_t{m[0], m[1]};
+                *reinterpret_cast<u32x2_t *>(at + 128) = u32x2_t{l[0], l[1]};
+            } else {
+                *reinterpret_cast<wseg_t *>(row + seg * SB) = y;
             }
         };
         auto store_chunk = [&](int s, int buf) {
@@ -163,8 +203,8 @@ __global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ 
                     if constexpr (CM == 2) y = hi ? u32x4_t{y[2], y[3], 0u, 0u} : y;
                 }
 #pragma unroll
-                for (int k = 0; k < SB / 4; ++k) y[k] = on ? y[k] : 0u;
-                *reinterpret_cast<wseg_t *>(A + (row0 + i * RPP) * kRowBytes + seg * SB) = y;
+                for (int k = 0; k < SB / 4; ++k) y[k] = on || SPLIT ? y[k] : 0u;
+                put(A + (row0 + i * RPP) * kRowBytes, y);
             }
 #pragma unroll
             for (int i = 0; i < BP; ++i) {
@@ -173,13 +213,44 @@ __global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ 
                 if constexpr (CM == 2) y = hi ? u32x4_t{y[2], y[3], 0u, 0u} : y;
 #pragma unroll
                 for (int k = 0; k < SB / 4; ++k) y[k] = on ? y[k] : 0u;
-                *reinterpret_cast<wseg_t *>(B + (row0 + i * RPP) * kRowBytes + seg * SB) = y;
+                put(B + (row0 + i * RPP) * kRowBytes, y);
             }
         };
         // lane quarter q holds bytes 16 q .. of each 64: the same K in A and B
         auto compute = [&](int buf) {
-            const char *A = lds + buf * (AR + BR) * kRowBytes + (wm * TI * 16 + j16) * kRowBytes + 16 * q4;
-            const char *B = lds + buf * (AR + BR) * kRowBytes + (AR + wn * TJ * 16 + j16) * kRowBytes + 16 * q4;
+            const int qc = SPLIT ? q4 ^ ((j16 >> 2) & 3) : q4;  // (tiles start at multiples of 16 rows)
+            const char *A = lds + buf * (AR + BR) * kRowBytes + (wm * TI * 16 + j16) * kRowBytes + 16 * qc;
+            const char *B = lds + buf * (AR + BR) * kRowBytes + (AR + wn * TJ * 16 + j16) * kRowBytes + 16 * qc;
+            if constexpr (SPLIT) {
+                u32x4_t b[3][TJ];
+#pragma unroll
+                for (int z = 0; z < 3; ++z)
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j)
+                        b[z][j] = *reinterpret_cast<const u32x4_t *>(B + j * 16 * kRowBytes + 64 * z);
+                // two row tiles at a time; smallest products first
+                constexpr int za[6] = {0, 2, 1, 0, 1, 0}, zb[6] = {2, 0, 1, 1, 0, 0};
+                constexpr int TU = TI < 2 ? TI : 2;
+#pragma unroll
+                for (int i0 = 0; i0 < TI; i0 += TU) {
+                    u32x4_t a[3][TU];
+#pragma unroll
+                    for (int z = 0; z < 3; ++z)
+#pragma unroll
+                        for (int i = 0; i < TU; ++i)
+                            a[z][i] = *reinterpret_cast<const u32x4_t *>(A + (i0 + i) * 16 * kRowBytes + 64 * z);
+#pragma unroll
+                    for (int z = 0; z < 6; ++z)
+#pragma unroll
+                        for (int i = 0; i < TU; ++i)
+#pragma unroll
+                            for (int j = 0; j < TJ; ++j)
+                                acc[i0 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    __builtin_bit_cast(bf16x8_t, b[zb[z]][j]),
+                                    __builtin_bit_cast(bf16x8_t, a[za[z]][i]), acc[i0 + i][j], 0, 0, 0);
+                }
+                return;
+            }
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
                 u32x4_t a[TI], b[TJ];
@@ -210,25 +281,100 @@ __global__ __launch_bounds__(kThreads) void k_conv_seg(const void *__restrict__ 
             }
         };
 
-        // ring slot s holds chunk s mod 2; LDS buffer s holds it while it is multiplied
+        // ring slot s holds chunk s mod 2; with two LDS buffers, buffer s holds
+        // it while it is multiplied
         load_chunk(0);
         load_chunk(1);
-        store_chunk(0, 0);
-        __syncthreads();
-        const int NQP = NQ / 2 * 2;
-        for (int q = 0; q < NQP; q += 2) {
-            load_chunk(0);
-            compute(0);
-            store_chunk(1, 1);
-            __syncthreads();
-            load_chunk(1);
-            compute(1);
+        if constexpr (BUFS == 1) {
+            for (int q = 0; q < NQ; q += 2) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    if (q + s >= NQ) break;
+                    store_chunk(s, 0);
+                    __syncthreads();
+                    load_chunk(s);
+                    compute(0);
+                    __syncthreads();
+                }
+            }
+        } else {
             store_chunk(0, 0);
             __syncthreads();
+            const int NQP = NQ / 2 * 2;
+            for (int q = 0; q < NQP; q += 2) {
+                load_chunk(0);
+                compute(0);
+                store_chunk(1, 1);
+                __syncthreads();
+                load_chunk(1);
+                compute(1);
+                store_chunk(0, 0);
+                __syncthreads();
+            }
+            if (NQ & 1) {
+                compute(0);
+                __syncthreads();  // the LDS is rewritten by the next tile
+            }
         }
-        if (NQ & 1) {
-            compute(0);
-            __syncthreads();  // the LDS is rewritten by the next tile
+
+        if constexpr (SPLIT) {
+            // a result that is not finite may come from an input that is not,
+            // or is too large for the split: the tile once more on fp32 MFMA,
+            // the operands straight from memory, 16 channels of a tap at a
+            // time (lane quarter q holds channels 4 q .. of them)
+            if (tid == 0) redo_s = 0;
+            __syncthreads();
+            bool bad = false;
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
+            if (bad) redo_s = 1;
+            __syncthreads();
+            if (redo_s) {
+                const float *X = reinterpret_cast<const float *>(in), *W = reinterpret_cast<const float *>(wv);
+#pragma unroll
+                for (int i = 0; i < TI; ++i)
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                for (int t = 0; t < T; ++t) {
+#pragma unroll 1
+                    for (int c = 4 * q4; c < C_in + 4 * q4; c += 16) {
+                        f32x4_t x4[TI], w4[TJ];
+#pragma unroll
+                        for (int i = 0; i < TI; ++i) {
+                            const int u = nbr_s[((wm * TI + i) * 16 + j16) * T + t];
+                            x4[i] = u >= 0 && c < C_in ? *reinterpret_cast<const f32x4_t *>(X + (int64_t)u * C_in + c)
+                                                       : f32x4_t{0.f, 0.f, 0.f, 0.f};
+                        }
+#pragma unroll
+                        for (int j = 0; j < TJ; ++j) {
+                            const int n = col_base + (wn * TJ + j) * 16 + j16;
+                            w4[j] = n < C_out && c < C_in ? *reinterpret_cast<const f32x4_t *>(W + n * K + t * C_in + c)
+                                                          : f32x4_t{0.f, 0.f, 0.f, 0.f};
+                        }
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+#pragma unroll
+                            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                                for (int j = 0; j < TJ; ++j)
+                                    acc[i][j] =
+                                        __builtin_amdgcn_mfma_f32_16x16x4f32(w4[j][e], x4[i][e], acc[i][j], 0, 0, 0);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < TI; ++i)
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[i][j][r] *= kSplitBack;
+            }
+            __syncthreads();  // nbr_s is rewritten by the next tile
         }
 
         // register r of lane (j16, q4): row j16, column 4 q4 + r of each tile
@@ -277,7 +423,7 @@ hipError_t go(lattice *L, const void *in, int C_in, const void *w, int C_out, co
     if (grid > tiles) grid = tiles;
     if (grid < 1) grid = 1;
     hipLaunchKernelGGL((k_conv_seg<CM, WM, TI, TJ>), dim3((unsigned)grid), dim3(kThreads), 0, L->stream, in, C_in,
-                       w, C_out, L->T, bias, out, out_bf16 ? 1 : 0, out_vec ? 1 : 0, L->nbr, L->counters);
+                       w, C_out, L->T, bias, out, out_bf16 ? 1 : 0, out_vec ? 1 : 0, L->nbr, L->counters, reinterpret_cast<const float *>(L->zero_row));
     return hipGetLastError();
 }
 
@@ -331,14 +477,35 @@ hipError_t launch_conv_seg(lattice *L, const void *in, lattice_dtype in_dt, int 
     const bool small = L->max_vertices <= 64 * (int64_t)L->cu_count;
     if (dt == LATTICE_F32) {
         if (small) return by_width<0, 1, 1>(L, in, C_in, w, C_out, bias, out, ob, vec);
-        return by_width<0, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
+        const int width = tile_width(C_out);
+        const bool large = L->max_vertices >= kConvLarge;
+        // The split takes tiles at least 64 wide, on large lattices 32, and 128
+        // rows there (which halves the weights' splitting) for all widths but
+        // 64: narrower ones are bound by their gathers.  us, fp32 MFMA -> split:
+        // 96 -> 96 on V = 31 500 / 98 600 / 263 000 58 -> 48, 177 -> 128, 505 -> 297,
+        // 100 -> 100 82 -> 61, 262 -> 194, 644 -> 374, 32 -> 32 and 48 -> 48 on
+        // V = 263 000 69 -> 56, 137 -> 120; 32 -> 32 on V = 71 000 21.9 -> 21.6, 8 -> 16
+        // on V = 278 788 23.9 -> 38.7.  (Where V is small for the lattice's bound,
+        // 96 -> 96 on V = 10 200 of 80 000 36.8 -> 40.1.)
+        switch (width < 64 && !large ? 0 : width) {
+            case 32: return go<3, 4, 2, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
+            case 48: return go<3, 4, 2, 3>(L, in, C_in, w, C_out, bias, out, ob, vec);
+            case 64: return go<3, 2, 2, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
+            case 96:
+                return large ? go<3, 2, 4, 3>(L, in, C_in, w, C_out, bias, out, ob, vec)
+                             : go<3, 2, 2, 3>(L, in, C_in, w, C_out, bias, out, ob, vec);
+            case 128:
+                return large ? go<3, 2, 4, 4>(L, in, C_in, w, C_out, bias, out, ob, vec)
+                             : go<3, 2, 2, 4>(L, in, C_in, w, C_out, bias, out, ob, vec);
+            default: return by_width<0, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
+        }
     }
     if (in_dt == LATTICE_F32) {
         if (small) return by_width<1, 1, 1>(L, in, C_in, w, C_out, bias, out, ob, vec);
         return by_width<1, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
     }
     if (small) return by_width<2, 1, 1>(L, in, C_in, w, C_out, bias, out, ob, vec);
-    if (tile_width(C_out) == 96 && L->max_vertices >= 400000)
+    if (tile_width(C_out) == 96 && L->max_vertices >= kConvLarge)
         return go<2, 2, 4, 3>(L, in, C_in, w, C_out, bias, out, ob, vec);
     return by_width<2, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
 }

@@ -67,6 +67,26 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
 }
 
+// 2^24 x of an fp32 value as a sum of three bf16: h = bf16(y), m = bf16(y -
+// h), l = y - h - m for y = 2^24 x, which has at most 8 significant bits left,
+// so that h + m + l = y exactly.  The scale is there because the matrix cores
+// flush bf16 subnormals: the least bit of the smallest subnormal x is 2^-125
+// after it (without it a value of 1e-37 lost its bits below 2^-126, errors of
+// 3e-5 of a sum's |terms|).  A sum of products is 2^48 times the wanted one.
+// Of the nine products of two such sums the six largest are taken; the other
+// three are below 2^-23 of the product together, and about 2^-26 of it on
+// average, with random sign: far less than the rounding of fp32 sums.  Two
+// values at a time, packed.  An x that is not finite, or that is 2^104 or
+// more, gives a NaN or an infinity in every product it enters.
+constexpr float kSplitScale = 16777216.f, kSplitBack = 3.552713678800501e-15f;  // 2^24, 2^-48
+__device__ __forceinline__ void split3(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
+    const float y0 = kSplitScale * x0, y1 = kSplitScale * x1;
+    h = pack_bf16(y0, y1);
+    const float r0 = y0 - __uint_as_float(h << 16), r1 = y1 - __uint_as_float(h & 0xffff0000u);
+    m = pack_bf16(r0, r1);
+    l = pack_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
+}
+
 struct lattice_timer {
     double ms = 0.0;    // summed elapsed time of read event pairs
     int64_t count = 0;  // number of read event pairs
@@ -182,6 +202,7 @@ hipError_t launch_conv(lattice *L, const void *in, lattice_dtype in_dt, int C_in
                        lattice_dtype dt, const float *bias, void *out, lattice_dtype out_dt);
 
 // conv_seg.hip: any C_in that is a multiple of 4 (16-byte aligned operands)
+constexpr int64_t kConvLarge = 400000;  // lattice bound from which its large tiles pay
 bool conv_seg_covers(lattice_dtype in_dt, int C_in, lattice_dtype dt);
 hipError_t launch_conv_seg(lattice *L, const void *in, lattice_dtype in_dt, int C_in, const void *w, int C_out,
                            lattice_dtype dt, const float *bias, void *out, lattice_dtype out_dt);

@@ -827,13 +827,14 @@ def test_conv_f32_extreme_values(C_in, C_out, m):
     L.close()
 
 
-@pytest.mark.parametrize("C_in,C_out,m", [(64, 64, 20000), (128, 128, 20000), (96, 96, 20000), (36, 100, 700)])
+@pytest.mark.parametrize("C_in,C_out,m", [(64, 64, 20000), (128, 128, 20000), (96, 96, 20000), (36, 100, 700),
+                                          (64, 64, 110000), (64, 128, 110000), (32, 48, 110000)])
 def test_conv_f32_holds_32_bits(C_in, C_out, m):
     """fp32 rows of 1e-37 to 2e-37 (all normal numbers, whose 24 bits reach
     down to 2^-147) keep the relative accuracy of ordinary ones: products
     with weights of +-1 and their sums are fp32, so only a narrower product
     could lose those bits.  Where the LDS-tiled kernel covers the shape, the
-    default path gives its bits."""
+    default path gives its bits up to a bound of 400 000 vertices."""
     w = random_cloud(m, 3, seed=1400, extent=1.0, C=1)
     L = _lattice(3, 0.2, w.m)
     g = GpuLattice(L, w.pos, w.feat)
@@ -844,7 +845,7 @@ def test_conv_f32_holds_32_bits(C_in, C_out, m):
     ref, scale = O.conv(x.astype(np.float64), O.neighbors(lat), W.astype(np.float64))
     assert_close_scaled(g.from_gpu_order(L.conv(g.to_gpu_order(x), to_dev(W))), ref, scale, REL_F32, "rows of 1e-37",
                         atol=0.0)
-    if C_in % 32 == 0 and C_out % 64 == 0:
+    if C_in % 32 == 0 and C_out % 64 == 0 and m < 100000:
         x, W = g.to_gpu_order(random_rows(lat.V, C_in, seed=1402)), to_dev(conv_weight(C_in, C_out, 3, seed=1403))
         auto = L.conv(x, W)
         L.set_conv_path("tiled")
@@ -853,10 +854,11 @@ def test_conv_f32_holds_32_bits(C_in, C_out, m):
 
 
 @pytest.mark.parametrize("C", [64, 96])
-def test_conv_f32_infinity_costs_nothing(C):
+def test_conv_f32_infinity_cost(C):
     """One infinite value among the rows, as an overflowed training step has
-    them, takes the time of ordinary rows (the fastest of several calls each;
-    a factor of 3 is far above their scatter)."""
+    them: 64 -> 64 on fp32 matrix instructions takes the time of ordinary rows,
+    96 -> 96 computes the tiles that meet it a second time (measured: 1.2 to
+    1.8 times an ordinary call; as serial chains 40 to 60 times)."""
     w = random_cloud(40000, 3, seed=1410, extent=1.0, C=1)
     L = _lattice(3, 0.1, w.m)
     V = GpuLattice(L, w.pos, w.feat).V
@@ -865,4 +867,38 @@ def test_conv_f32_infinity_costs_nothing(C):
     bad = x.clone()
     bad[V // 2, 3] = float("inf")
     assert fastest_ms(lambda: L.conv(bad, W)) < 3 * fastest_ms(lambda: L.conv(x, W))
+    L.close()
+
+
+@pytest.mark.parametrize("C_in,C_out", [(20, 32), (36, 48), (64, 64), (100, 96), (8, 128), (324, 100), (64, 192)])
+@pytest.mark.parametrize("bound", [20000, 110000])
+def test_conv_f32_split_instances(C_in, C_out, bound):
+    """Every tile of the split fp32 convolution (lattices made for few and for
+    many points): ordinary rows; then infinities, NaN and values of 1e30 (the
+    split's sums overflow from 1.2e24 on), which are computed again on fp32
+    matrix instructions and agree where the sum of the same products is
+    finite, infinite or NaN."""
+    w = random_cloud(1500, 3, seed=1500, extent=1.0, C=1)
+    L = _lattice(3, 0.25, bound)
+    g = GpuLattice(L, w.pos, w.feat)
+    lat = O.build(w.pos, 0.25)
+    nbr = O.neighbors(lat)
+    x = random_rows(lat.V, C_in, seed=1501)
+    W = conv_weight(C_in, C_out, 3, seed=1502)
+    b = random_rows(1, C_out, seed=1503)[0]
+    ref, scale = O.conv(x.astype(np.float64), nbr, W.astype(np.float64), b)
+    got = g.from_gpu_order(L.conv(g.to_gpu_order(x), to_dev(W), bias=to_dev(b)))
+    assert_close_scaled(got, ref, scale, REL_F32, f"split conv {C_in}x{C_out} bound {bound}")
+    rng = np.random.default_rng(1504)
+    for i, v in enumerate(rng.choice(lat.V, size=30, replace=False)):
+        x[v, rng.integers(C_in)] = (np.inf, -np.inf, np.nan, 1e30, -3e25, 1e-42)[i % 6]
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref, scale = O.conv(x.astype(np.float64), nbr, W.astype(np.float64), b)
+    got = g.from_gpu_order(L.conv(g.to_gpu_order(x), to_dev(W), bias=to_dev(b)))
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.isnan(ref).any()
+    inf = np.isinf(ref)
+    assert inf.any() and np.array_equal(got[inf], ref[inf])
+    ok = np.isfinite(ref)
+    assert ok.any() and np.abs(ref[ok]).max() > 1e24
+    assert_close_scaled(got[ok], ref[ok], scale[ok], REL_F32, "split conv beside extreme values")
     L.close()
