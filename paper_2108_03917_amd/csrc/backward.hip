@@ -224,13 +224,14 @@ __global__ __launch_bounds__(kBlock) void k_conv_wgrad(const void *__restrict__ 
 // workgroup takes kTaps taps of its chunk, so that a step's g rows are loaded
 // and staged once for three products, with two steps' rows in flight and two
 // workgroups per CU (a tap per workgroup, one step ahead and four per CU kept
-// fewer loads in flight and read g nine times).  With its reduction, us, that
-// kernel -> this one (fp32: fp32 MFMA 32x32x2 -> the split): V = 278 788, T = 9:
-// bf16 64 -> 64 119 -> 79, 128 -> 128 407 -> 262, fp32 64 -> 64 256 -> 167, 128 -> 128
-// 920 -> 579; V = 70 989: 41 -> 34, 113 -> 82, 78 -> 58, 245 -> 168; V = 5 211: 18.7 ->
-// 17.2, 23.9 -> 23.5, 23.5 -> 21.6, 36.7 -> 37.2.  The largest, bf16 128 -> 128, runs
-// at 313 TFLOP/s of the 2 400 the matrix cores reach: the transposing stores to
-// LDS and the gathers' latency.
+// fewer loads in flight and read g nine times).  With its reduction, us, T = 9,
+// that kernel -> this one (fp32: fp32 MFMA 32x32x2 -> the split): V = 293 290: bf16
+// 64 -> 64 121 -> 80, 128 -> 128 425 -> 277, from fp32 rows 205 -> 125, 753 -> 457, fp32
+// 267 -> 160, 966 -> 632; V = 68 199: 37 -> 31, 107 -> 76, 56 -> 41, 170 -> 110, 73 -> 51,
+// 235 -> 154; V = 5 752: 18.5 -> 16.2, 23.1 -> 24.5, 20.9 -> 17.2, 29.0 -> 27.5, 23.3 ->
+// 20.7, 36.5 -> 34.7.  The largest, bf16 128 -> 128, runs at 312 TFLOP/s of the
+// 2 400 the matrix cores reach: the transposing stores to LDS and the gathers'
+// latency.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef u32x4_t u32x4_a4_t __attribute__((aligned(4)));
@@ -281,7 +282,7 @@ struct Row4<false> {
 //     and 16 of several.  In multiples of 16: the reduction's four groups load
 //     four partials at a time.
 //   * One tile, or two in bf16: no more than `one`, a workgroup per CU, before
-//     a chunk has 3 (fp32) or 4.5 steps with two per CU: a second workgroup on
+//     a chunk has 2.75 (fp32) or 4.5 steps with two per CU: a second workgroup on
 //     some CUs only makes those the last to end.
 // us, T = 9, one-tap kernel | three taps, at least 2 tiles steps a chunk and 8
 // chunks | this rule: bf16 64 -> 64 V = 3 000 17.9 | 14.3 | 14.2, 11 000 19.7 | 24.4
@@ -311,7 +312,7 @@ ChunkRule chunk_rule(int nch, int tiles, bool bf16) {
     r.per = bf16 && !single ? 6 : 3;
     r.low = single ? 48 : 16;
     r.one = (single || (bf16 && tiles == 2)) && nch >= 32 ? nch / 2 / 8 * 8 : nch;
-    r.two_from = (int64_t)nch * (bf16 ? 9 : 6) / 2;
+    r.two_from = (int64_t)nch * (bf16 ? 18 : 11) / 4;
     return r;
 }
 
@@ -625,11 +626,8 @@ int wgrad_chunks(const lattice *L, const void *g, lattice_dtype g_dt, int C_out,
     const int64_t room = LATTICE_NOALLOC_WORKSPACE_BYTES - (n * 4 + 255) / 256 * 256;
     const int64_t fit = room / ((n + C_out) * 4) / 8 * 8;
     // rounded down: 528 workgroups over 512 places took a second round (fp32
-    // 32 -> 32 on V = 278 788 246 us against 167 for 64 -> 64); many chunks to
-    // the reduction's 16 (fp32 64 -> 64 on V = 40 000 in 168 and 160 chunks: 40.3
-    // and 38.2)
-    int64_t want = 2 * (int64_t)L->cu_count / (tiles * ((L->T + kTaps - 1) / kTaps));
-    want = want >= 64 ? want / 16 * 16 : want / 8 * 8;
+    // 32 -> 32 on V = 278 788 246 us against 167 for 64 -> 64)
+    int64_t want = 2 * (int64_t)L->cu_count / (tiles * ((L->T + kTaps - 1) / kTaps)) / 8 * 8;
     if (want > fit) want = fit;
     if (want < 8) want = 8;
     if (nch <= fit && wgrad_taps(g, g_dt, C_out, x, x_dt, C_in, dt)) nch = want;

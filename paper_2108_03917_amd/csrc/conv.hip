@@ -1386,7 +1386,8 @@ hipError_t dispatch_out(lattice *L, const void *in, lattice_dtype in_dt, int C_i
         if (try_rs<OUT_BF16>(L, in, C_in, w, C_out, bias, out, &err)) return err;
     }
     // fp32 64 -> 64: the register-resident kernel (K split over two
-    // wavefronts) only on request; the LDS-tiled kernel is faster there
+    // wavefronts) only on request; the LDS-tiled kernel is faster there, and
+    // the split on large lattices
     if (aligned && out_vec && path == LATTICE_CONV_RS && !bf16 && !in_bf16 && L->T == 9 && C_in == 64 && C_out == 64)
         return launch_rs<false, OUT_BF16, 9, 64, 64, 2>(L, in, w, bias, out);
     // Of the other shapes, the segment-walking kernel takes (AUTO) every bf16

@@ -467,13 +467,15 @@ hipError_t launch_conv_seg(lattice *L, const void *in, lattice_dtype in_dt, int 
                            lattice_dtype dt, const float *bias, void *out, lattice_dtype out_dt) {
     const bool ob = out_dt == LATTICE_BF16;
     const bool vec = C_out % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & (ob ? 7 : 15)) == 0;
-    // Rows per tile (V is on the device: the lattice's bound stands for it).
+    // Rows per tile (V is on the device: the lattice's bound stands for it; a
+    // lattice far below its bound pays for it, bf16 96 -> 96 on V = 2 900 in tiles
+    // of 32, 64 and 128 rows 10.8, 13.0 and 17.3).
     // Clouds whose bound gives fewer tiles of 64 rows than CUs take half
     // tiles (one part-segmentation object, V = 5 211, us: bf16 64 -> 96 8.7
     // against 7.8, fp32 96 -> 96 32.8 against 22.5); 96-wide tiles of large
     // lattices take 128 rows, which halves the weight reads (bf16 96 -> 96 on
-    // V = 278 788: 131 against 109, on V = 143 537: 74 against 68; on
-    // V = 70 989 35 against 38, so from 400 000 on).
+    // V = 278 788: 131 against 109, on V = 143 537: 74 against 68, both with
+    // bounds above 500 000; on V = 70 989 of 160 000 35 against 38).
     const bool small = L->max_vertices <= 64 * (int64_t)L->cu_count;
     if (dt == LATTICE_F32) {
         if (small) return by_width<0, 1, 1>(L, in, C_in, w, C_out, bias, out, ob, vec);
