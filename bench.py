@@ -546,7 +546,7 @@ def cpu_baseline(w, budget_s=20.0, dw=None, train=False, unet=False, pointnet=No
 STAGE_SOURCES = {
     "splat": ["splat.hip", "keys.h", "internal.h"],
     "neighbors": ["neighbors.hip", "keys.h", "internal.h"],
-    "conv": ["conv.hip", "internal.h"],
+    "conv": ["conv.hip", "conv_seg.hip", "internal.h"],
     "slice": ["slice.hip", "internal.h"],
     "deform": ["deform.hip", "internal.h"],
 }

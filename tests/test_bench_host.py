@@ -2,6 +2,7 @@
 algorithmic work, the roofline classification, the stored traffic table,
 and the one-GPU rule."""
 import functools
+import os
 import subprocess
 import sys
 import types
@@ -74,3 +75,23 @@ def test_stored_traffic_matches_the_sources():
 def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, "bench.py", "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode == 2 and "one GPU only" in r.stderr
+
+
+def test_stage_sources_hold_their_kernels():
+    """Every kernel that a stored counter entry names is defined in one of its
+    stage's sources, and so is every launcher that those dispatch the same
+    stage to: a change there makes the entry stale."""
+    import json
+    import re
+
+    csrc = os.path.join(bench.ROOT, "paper_2108_03917_amd", "csrc")
+    text = {f: open(os.path.join(csrc, f)).read() for f in os.listdir(csrc) if f.endswith((".hip", ".h"))}
+    for key, e in json.load(open(bench.TRAFFIC_FILE))["entries"].items():
+        stage = key.split("/")[1]
+        files = bench.STAGE_SOURCES["conv" if stage.startswith("conv") else stage]
+        for k in e["kernels"]:
+            name = k.split("<")[0]
+            assert any(re.search(r"\b%s\(" % name, text[f]) for f in files), (key, k)
+    for called in re.findall(r"\blaunch_conv_\w+(?=\()", text["conv.hip"]):
+        where = [f for f in text if f.endswith(".hip") and re.search(r"hipError_t %s\(" % called, text[f])]
+        assert where and set(where) <= set(bench.STAGE_SOURCES["conv"]), called
