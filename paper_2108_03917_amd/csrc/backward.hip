@@ -599,7 +599,8 @@ __global__ __launch_bounds__(kBlock) void k_flip_weights(const E *__restrict__ w
 
 }  // namespace
 
-// Whether k_conv_wgrad_taps takes these operands.
+// Whether the rows take loads of four channels, and whether k_conv_wgrad_taps
+// takes the operands.
 static bool wgrad_vec(const void *g, lattice_dtype g_dt, int C_out, const void *x, lattice_dtype x_dt, int C_in) {
     return C_out % 4 == 0 && C_in % 4 == 0 && (reinterpret_cast<uintptr_t>(g) & (g_dt == LATTICE_BF16 ? 7 : 15)) == 0 &&
            (reinterpret_cast<uintptr_t>(x) & (x_dt == LATTICE_BF16 ? 7 : 15)) == 0;
