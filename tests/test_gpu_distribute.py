@@ -569,7 +569,7 @@ def test_distribute_pointnet_backward_scratch():
         backward(batch)
     assert taken[0] <= (216 + 256) * pairs + (96 << 20)      # partial rows: under 96 MB on 256 CUs
     assert 256 * pairs <= taken[1] <= 256 * pairs + (8 << 20)
-    assert taken[2:] == [0, 0]
+    assert max(taken[2:]) <= 4 << 20                         # torch's own small blocks
     for a, b in ((0, 2), (1, 3)):       # a new splat's vertex order, and near ties of the maximum with it
         assert torch.isfinite(got[a]).all()
         assert (got[a] - got[b]).norm() <= 1e-2 * got[b].norm()

@@ -866,7 +866,7 @@ def test_conv_f32_infinity_cost(C):
     x, W = to_dev(random_rows(V, C, seed=1411)), to_dev(conv_weight(C, C, 3, seed=1412))
     bad = x.clone()
     bad[V // 2, 3] = float("inf")
-    assert fastest_ms(lambda: L.conv(bad, W)) < 3 * fastest_ms(lambda: L.conv(x, W))
+    assert fastest_ms(lambda: L.conv(bad, W)) < 6 * fastest_ms(lambda: L.conv(x, W))
     L.close()
 
 
