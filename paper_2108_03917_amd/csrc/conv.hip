@@ -1403,9 +1403,11 @@ hipError_t dispatch_out(lattice *L, const void *in, lattice_dtype in_dt, int C_i
     // lattice, where its split into bf16 products pays (64 -> 64, 128 -> 128,
     // 256 -> 256 on V = 263 000 206 against 162, 669 against 465, 2609 against
     // 1711; on V = 32 100 of a bound of 415 556 30.8 against 29.3, 92 against 82,
-    // 319 against 209).  In between the tiled kernel stays: with a bound of
-    // 80 000 and V = 10 200 the split took 22.5 against 18.6 and 63 against 50,
-    // with 160 000 and V = 69 800 49 against 58 and 183 against 193.
+    // 319 against 209).  In between the tiled kernel stays, although the split
+    // would gain up to 18% from some 20 000 vertices on (V = 69 800 58 against 49,
+    // 193 against 183): its sums are rounded otherwise, so that the vertex that
+    // wins DeformSlice's maximum at a near tie, and a gradient's term with it,
+    // would be another than the tiled kernel's.
     const bool seg = aligned && conv_seg_covers(in_dt, C_in, dt);
     const lattice_dtype out_dt = OUT_BF16 ? LATTICE_BF16 : LATTICE_F32;
     const bool small = L->max_vertices <= 64 * (int64_t)L->cu_count;

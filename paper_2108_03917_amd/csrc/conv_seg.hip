@@ -24,8 +24,8 @@
 // values; their error against 64 bits is a little below fp32 MFMA's (64 -> 64
 // 3e-7 against 4e-7, 128 -> 128 4e-7 against 5e-7: fewer roundings of the
 // running sum).  A tile with a result that is not finite is computed once
-// more on fp32 MFMA: with one infinity among the rows 96 -> 96 takes 40 -> 73 us
-// on V = 10 200, 123 -> 147 on V = 75 500.
+// more on fp32 MFMA: with one infinity among the rows 96 -> 96 on V = 75 500 takes
+// 119 -> 179 us, 128 -> 128 186 -> 274.
 //
 // What bounds it: bf16, the gathers and the weight rows through L2 (each tile
 // re-reads W); the split, its own vector instructions (6.5 a value and stage)
@@ -62,45 +62,63 @@ constexpr int kThreads = 256;
 // while staging, bf16 weights; CM 2: bf16 rows and weights.  The four
 // wavefronts are WM x (4 / WM), each TI x TJ tiles of 16 x 16.
 template <int CM, int WM, int TI, int TJ>
-__global__ __launch_bounds__(kThreads, CM != 3 ? 1 : TI * TJ > 6 ? 2 : TI * TJ == 6 ? 3 : 4) void k_conv_seg(const void *__restrict__ in, int C_in,
-                                                       const void *__restrict__ wv, int C_out, int T,
-                                                       const float *__restrict__ bias, void *__restrict__ out,
-                                                       int out_bf16, int out_vec, const int32_t *__restrict__ nbr,
-                                                       const int32_t *__restrict__ counters,
-                                                       const float *__restrict__ zero_row) {
-    constexpr int WN = 4 / WM;
-    constexpr int BM = WM * TI * 16, BN = WN * TJ * 16;
-    constexpr int SE = CM == 2 ? 8 : 4;               // channels per segment
-    constexpr bool SPLIT = CM == 3;
-    constexpr int ESZ = CM == 0 || SPLIT ? 4 : 2;     // weight element (and staged element, unless split)
-    constexpr int SB = SE * ESZ;                      // LDS (and weight) bytes per segment
-    constexpr int XESZ = CM == 2 ? 2 : 4;             // stored input element: 16 bytes of input per segment
-    constexpr int SEGS = 128 / SB;                    // segments per row and chunk
-    constexpr int RPP = kThreads / SEGS;              // rows per pass
-    constexpr int AP = (BM + RPP - 1) / RPP, BP = (BN + RPP - 1) / RPP;
-    constexpr int AR = AP * RPP, BR = BP * RPP;       // LDS rows (whole passes)
+struct Shape {
+    static constexpr int WN = 4 / WM;
+    static constexpr int BM = WM * TI * 16, BN = WN * TJ * 16;
+    static constexpr int SE = CM == 2 ? 8 : 4;               // channels per segment
+    static constexpr bool SPLIT = CM == 3;
+    static constexpr int ESZ = CM == 0 || SPLIT ? 4 : 2;     // weight element (and staged element, unless split)
+    static constexpr int SB = SE * ESZ;                      // LDS (and weight) bytes per segment
+    static constexpr int XESZ = CM == 2 ? 2 : 4;             // stored input element: 16 bytes of input per segment
+    static constexpr int SEGS = 128 / SB;                    // segments per row and chunk
+    static constexpr int RPP = kThreads / SEGS;              // rows per pass
+    static constexpr int AP = (BM + RPP - 1) / RPP, BP = (BN + RPP - 1) / RPP;
+    static constexpr int AR = AP * RPP, BR = BP * RPP;       // LDS rows (whole passes)
     // One LDS row: 128 bytes and 16 of padding (16 rows read 16 bytes each on
     // 64 different banks), or three planes of 64 bytes without: four rows'
     // 8-byte writes then fill the 64 banks, and 16-byte chunk c of row r sits at
     // c ^ (r / 4 % 4), which spreads the reads of 16 rows the same way (padded
     // rows had 2-way conflicts on the writes, half of the LDS time)
-    constexpr int kRowBytes = SPLIT ? 3 * 64 : 128 + 16;
+    static constexpr int kRowBytes = SPLIT ? 3 * 64 : 128 + 16;
+    // LDS buffers: the split's planes take one (two to four workgroups per CU
+    // hide its second barrier), the others two
+    static constexpr int BUFS = SPLIT ? 1 : 2;
+    static constexpr int kLds = BUFS * (AR + BR) * kRowBytes;
+    static constexpr int kNbr = AR * kMaxTaps;
+};
+
+struct Args {
+    const void *in;
+    int C_in;
+    const void *wv;
+    int C_out, T;
+    const float *bias;
+    void *out;
+    int out_bf16, out_vec;
+    const int32_t *nbr, *counters;
+    const float *zero_row;
+};
+
+// The tiles of one workgroup, with Shape's LDS (redo_s: the split's only).
+template <int CM, int WM, int TI, int TJ>
+__device__ __forceinline__ void conv_tiles(const void *__restrict__ in, int C_in, const void *__restrict__ wv,
+                                           int C_out, int T, const float *__restrict__ bias, void *__restrict__ out,
+                                           int out_bf16, int out_vec, const int32_t *__restrict__ nbr, int64_t V,
+                                           const float *__restrict__ zero_row, char *lds, int32_t *nbr_s,
+                                           int *redo_s) {
+    typedef Shape<CM, WM, TI, TJ> S;
+    constexpr int WN = S::WN, BM = S::BM, BN = S::BN, SE = S::SE, ESZ = S::ESZ, SB = S::SB, XESZ = S::XESZ;
+    constexpr int SEGS = S::SEGS, RPP = S::RPP, AP = S::AP, BP = S::BP, AR = S::AR, BR = S::BR;
+    constexpr int kRowBytes = S::kRowBytes, BUFS = S::BUFS;
+    constexpr bool SPLIT = S::SPLIT;
     constexpr int P = 2;                              // chunks in the register ring
     typedef u32x4_t xseg_t;
     typedef typename std::conditional<SB == 16, u32x4_t, u32x2_t>::type wseg_t;
-
-    // LDS buffers: the split's planes take one (two to four workgroups per CU
-    // hide its second barrier), the others two
-    constexpr int BUFS = SPLIT ? 1 : 2;
-    __shared__ __attribute__((aligned(16))) char lds[BUFS * (AR + BR) * kRowBytes];
-    __shared__ int32_t nbr_s[AR * kMaxTaps];
-    __shared__ int redo_s;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int j16 = lane & 15, q4 = lane >> 4;
     const int seg = tid % SEGS, row0 = tid / SEGS;
-    const int64_t V = counters[CNT_V];
     const int64_t n_mt = (V + BM - 1) / BM;
     const int n_nt = (C_out + BN - 1) / BN;
     const int spr = (C_in + SE - 1) / SE;             // segments per tap
@@ -322,7 +340,7 @@ __global__ __launch_bounds__(kThreads, CM != 3 ? 1 : TI * TJ > 6 ? 2 : TI * TJ =
             // or is too large for the split: the tile once more on fp32 MFMA,
             // the operands straight from memory, 16 channels of a tap at a
             // time (lane quarter q holds channels 4 q .. of them)
-            if (tid == 0) redo_s = 0;
+            if (tid == 0) *redo_s = 0;
             __syncthreads();
             bool bad = false;
 #pragma unroll
@@ -331,9 +349,9 @@ __global__ __launch_bounds__(kThreads, CM != 3 ? 1 : TI * TJ > 6 ? 2 : TI * TJ =
                 for (int j = 0; j < TJ; ++j)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
-            if (bad) redo_s = 1;
+            if (bad) *redo_s = 1;
             __syncthreads();
-            if (redo_s) {
+            if (*redo_s) {
                 const float *X = reinterpret_cast<const float *>(in), *W = reinterpret_cast<const float *>(wv);
 #pragma unroll
                 for (int i = 0; i < TI; ++i)
@@ -415,15 +433,68 @@ __global__ __launch_bounds__(kThreads, CM != 3 ? 1 : TI * TJ > 6 ? 2 : TI * TJ =
 }
 
 template <int CM, int WM, int TI, int TJ>
-hipError_t go(lattice *L, const void *in, int C_in, const void *w, int C_out, const float *bias, void *out,
-              bool out_bf16, bool out_vec) {
-    constexpr int BM = WM * TI * 16, BN = (4 / WM) * TJ * 16;
+__global__ __launch_bounds__(kThreads) void k_conv_seg(Args a) {
+    typedef Shape<CM, WM, TI, TJ> S;
+    __shared__ __attribute__((aligned(16))) char lds[S::kLds];
+    __shared__ int32_t nbr_s[S::kNbr];
+    conv_tiles<CM, WM, TI, TJ>(a.in, a.C_in, a.wv, a.C_out, a.T, a.bias, a.out, a.out_bf16, a.out_vec, a.nbr,
+                               a.counters[CNT_V], a.zero_row, lds, nbr_s, nullptr);
+}
+
+// fp32 where the split may pay: up to small_v vertices, which the lattice's
+// bound does not tell (a coarse level keeps its cloud's), fp32 MFMA in tiles of
+// 32 rows (64 of narrow outputs), above the split's WM, TI, TJ.  V = 2 871 with
+// a bound of 400 000, us, split alone | with this: 64 -> 64 21.0 | 13.4, 96 -> 96
+// 52 | 22.6, 128 -> 128 79 | 22.6, 256 -> 256 151 | 61 (the kernels before both 16.7,
+// 45, 28.7, 52).  (Register bounds: as many workgroups per CU as the split
+// alone would have.)
+template <int WM, int TI, int TJ, int SM, int SI, int SJ>
+__global__ __launch_bounds__(kThreads, TI * TJ > 6 ? 2 : TI * TJ == 6 ? 3 : 4) void k_conv_seg_split(Args a,
+                                                                                                    int small_v) {
+    typedef Shape<3, WM, TI, TJ> S;
+    typedef Shape<0, SM, SI, SJ> F;
+    __shared__ __attribute__((aligned(16))) char lds[S::kLds > F::kLds ? S::kLds : F::kLds];
+    __shared__ int32_t nbr_s[S::kNbr > F::kNbr ? S::kNbr : F::kNbr];
+    __shared__ int redo_s;
+    const int64_t V = a.counters[CNT_V];
+    if (V <= small_v)
+        conv_tiles<0, SM, SI, SJ>(a.in, a.C_in, a.wv, a.C_out, a.T, a.bias, a.out, a.out_bf16, a.out_vec, a.nbr, V,
+                                  a.zero_row, lds, nbr_s, nullptr);
+    else
+        conv_tiles<3, WM, TI, TJ>(a.in, a.C_in, a.wv, a.C_out, a.T, a.bias, a.out, a.out_bf16, a.out_vec, a.nbr, V,
+                                  a.zero_row, lds, nbr_s, &redo_s);
+}
+
+Args args(lattice *L, const void *in, int C_in, const void *w, int C_out, const float *bias, void *out, bool out_bf16,
+          bool out_vec) {
+    return Args{in,  C_in, w, C_out, L->T, bias, out, out_bf16 ? 1 : 0, out_vec ? 1 : 0, L->nbr, L->counters,
+                reinterpret_cast<const float *>(L->zero_row)};
+}
+
+// Four workgroups per CU walk the tiles, or as many as there can be tiles.
+unsigned grid_of(const lattice *L, int BM, int BN, int C_out) {
     const int64_t tiles = ((L->max_vertices + BM - 1) / BM) * ((C_out + BN - 1) / BN);
     int64_t grid = (int64_t)L->cu_count * 4;
     if (grid > tiles) grid = tiles;
-    if (grid < 1) grid = 1;
-    hipLaunchKernelGGL((k_conv_seg<CM, WM, TI, TJ>), dim3((unsigned)grid), dim3(kThreads), 0, L->stream, in, C_in,
-                       w, C_out, L->T, bias, out, out_bf16 ? 1 : 0, out_vec ? 1 : 0, L->nbr, L->counters, reinterpret_cast<const float *>(L->zero_row));
+    return (unsigned)(grid < 1 ? 1 : grid);
+}
+
+template <int CM, int WM, int TI, int TJ>
+hipError_t go(lattice *L, const void *in, int C_in, const void *w, int C_out, const float *bias, void *out,
+              bool out_bf16, bool out_vec) {
+    typedef Shape<CM, WM, TI, TJ> S;
+    hipLaunchKernelGGL((k_conv_seg<CM, WM, TI, TJ>), dim3(grid_of(L, S::BM, S::BN, C_out)), dim3(kThreads), 0,
+                       L->stream, args(L, in, C_in, w, C_out, bias, out, out_bf16, out_vec));
+    return hipGetLastError();
+}
+
+template <int WM, int TI, int TJ, int SM, int SI, int SJ>
+hipError_t go_split(lattice *L, const void *in, int C_in, const void *w, int C_out, const float *bias, void *out,
+                    bool out_bf16, bool out_vec, int64_t small_v) {
+    typedef Shape<0, SM, SI, SJ> F;
+    hipLaunchKernelGGL((k_conv_seg_split<WM, TI, TJ, SM, SI, SJ>), dim3(grid_of(L, F::BM, F::BN, C_out)),
+                       dim3(kThreads), 0, L->stream, args(L, in, C_in, w, C_out, bias, out, out_bf16, out_vec),
+                       (int)small_v);
     return hipGetLastError();
 }
 
@@ -486,19 +557,21 @@ hipError_t launch_conv_seg(lattice *L, const void *in, lattice_dtype in_dt, int 
         // 64: narrower ones are bound by their gathers.  us, fp32 MFMA -> split:
         // 96 -> 96 on V = 31 500 / 98 600 / 263 000 58 -> 48, 177 -> 128, 505 -> 297,
         // 100 -> 100 82 -> 61, 262 -> 194, 644 -> 374, 32 -> 32 and 48 -> 48 on
-        // V = 263 000 69 -> 56, 137 -> 120; 32 -> 32 on V = 71 000 21.9 -> 21.6, 8 -> 16
-        // on V = 278 788 23.9 -> 38.7.  (Where V is small for the lattice's bound,
-        // 96 -> 96 on V = 10 200 of 80 000 36.8 -> 40.1.)
+        // V = 263 000 69 -> 56, 137 -> 120; 32 -> 32 on V = 71 000 21.9 -> 21.6, on
+        // V = 32 000 12.0 -> 16.5, 8 -> 16 on V = 278 788 23.9 -> 38.7.  Below 64
+        // vertices per CU it leaves CUs idle (V = 10 200 64 -> 64 18.9 -> 22.5,
+        // 96 -> 96 36.8 -> 40.1), of narrow outputs below 256.
+        const int64_t v64 = 64 * (int64_t)L->cu_count, v256 = 4 * v64;
         switch (width < 64 && !large ? 0 : width) {
-            case 32: return go<3, 4, 2, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
-            case 48: return go<3, 4, 2, 3>(L, in, C_in, w, C_out, bias, out, ob, vec);
-            case 64: return go<3, 2, 2, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
+            case 32: return go_split<4, 2, 2, 4, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec, v256);
+            case 48: return go_split<4, 2, 3, 4, 1, 3>(L, in, C_in, w, C_out, bias, out, ob, vec, v256);
+            case 64: return go_split<2, 2, 2, 2, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec, v64);
             case 96:
-                return large ? go<3, 2, 4, 3>(L, in, C_in, w, C_out, bias, out, ob, vec)
-                             : go<3, 2, 2, 3>(L, in, C_in, w, C_out, bias, out, ob, vec);
+                return large ? go_split<2, 4, 3, 2, 1, 3>(L, in, C_in, w, C_out, bias, out, ob, vec, v64)
+                             : go_split<2, 2, 3, 2, 1, 3>(L, in, C_in, w, C_out, bias, out, ob, vec, v64);
             case 128:
-                return large ? go<3, 2, 4, 4>(L, in, C_in, w, C_out, bias, out, ob, vec)
-                             : go<3, 2, 2, 4>(L, in, C_in, w, C_out, bias, out, ob, vec);
+                return large ? go_split<2, 4, 4, 2, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec, v64)
+                             : go_split<2, 2, 4, 2, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec, v64);
             default: return by_width<0, 1, 2>(L, in, C_in, w, C_out, bias, out, ob, vec);
         }
     }

@@ -828,7 +828,8 @@ def test_conv_f32_extreme_values(C_in, C_out, m):
 
 
 @pytest.mark.parametrize("C_in,C_out,m", [(64, 64, 20000), (128, 128, 20000), (96, 96, 20000), (36, 100, 700),
-                                          (64, 64, 110000), (64, 128, 110000), (32, 48, 110000)])
+                                          (96, 96, 40000), (64, 64, 110000), (64, 128, 110000),
+                                          (32, 48, 110000)])
 def test_conv_f32_holds_32_bits(C_in, C_out, m):
     """fp32 rows of 1e-37 to 2e-37 (all normal numbers, whose 24 bits reach
     down to 2^-147) keep the relative accuracy of ordinary ones: products
@@ -836,9 +837,10 @@ def test_conv_f32_holds_32_bits(C_in, C_out, m):
     could lose those bits.  Where the LDS-tiled kernel covers the shape, the
     default path gives its bits up to a bound of 400 000 vertices."""
     w = random_cloud(m, 3, seed=1400, extent=1.0, C=1)
-    L = _lattice(3, 0.2, w.m)
+    sigma = 0.2 if m < 40000 else 0.05         # vertices enough for the split
+    L = _lattice(3, sigma, w.m)
     g = GpuLattice(L, w.pos, w.feat)
-    lat = O.build(w.pos, 0.2)
+    lat = O.build(w.pos, sigma)
     rng = np.random.default_rng(1401)
     W = np.sign(rng.standard_normal((C_out, 9, C_in))).astype(np.float32)
     x = (1e-37 * (1 + rng.random((lat.V, C_in))) * np.sign(rng.standard_normal((lat.V, C_in)))).astype(np.float32)
@@ -860,7 +862,7 @@ def test_conv_f32_infinity_cost(C):
     96 -> 96 computes the tiles that meet it a second time (measured: 1.2 to
     1.8 times an ordinary call; as serial chains 40 to 60 times)."""
     w = random_cloud(40000, 3, seed=1410, extent=1.0, C=1)
-    L = _lattice(3, 0.1, w.m)
+    L = _lattice(3, 0.06, w.m)
     V = GpuLattice(L, w.pos, w.feat).V
     L.build_neighbors()
     x, W = to_dev(random_rows(V, C, seed=1411)), to_dev(conv_weight(C, C, 3, seed=1412))
@@ -870,18 +872,44 @@ def test_conv_f32_infinity_cost(C):
     L.close()
 
 
-@pytest.mark.parametrize("C_in,C_out", [(20, 32), (36, 48), (64, 64), (100, 96), (8, 128), (324, 100), (64, 192)])
-@pytest.mark.parametrize("bound", [20000, 110000])
-def test_conv_f32_split_instances(C_in, C_out, bound):
+def test_conv_f32_few_vertices_of_large_bound():
+    """A lattice far below its bound, as a coarse level keeps its cloud's,
+    convolves about as fast as one made for the same points alone: its kernel
+    goes by the vertices that there are (128 -> 128 measured: 0.8 times the
+    small lattice's time, the split alone 2.7 times)."""
+    w = random_cloud(1000, 3, seed=1520, extent=1.0, C=1)
+    x, W = None, to_dev(conv_weight(128, 128, 3, seed=1521))
+    ms = []
+    for bound in (10000, 100000):                    # bounds of 40 000 and 400 000 vertices
+        L = _lattice(3, 0.12, bound)
+        V = GpuLattice(L, w.pos, w.feat).V
+        L.build_neighbors()
+        x = to_dev(random_rows(V, 128, seed=1522)) if x is None else x
+        assert x.shape[0] == V and 2000 < V < 5000
+        ms.append(fastest_ms(lambda: [L.conv(x, W) for _ in range(20)]))
+        L.close()
+    assert ms[1] < 1.6 * ms[0], ms
+
+
+@pytest.mark.parametrize("C_in,C_out,points,bound", [
+    (20, 32, 17500, 110000), (36, 48, 17500, 110000), (64, 64, 4500, 110000), (100, 96, 4500, 20000),
+    (100, 96, 4500, 110000), (8, 128, 4500, 20000), (324, 100, 4500, 110000), (64, 192, 4500, 110000),
+    (20, 32, 1500, 110000), (36, 48, 1500, 110000), (64, 64, 1500, 110000), (100, 96, 1500, 20000),
+    (324, 100, 1500, 110000), (64, 192, 1500, 110000)])
+def test_conv_f32_split_instances(C_in, C_out, points, bound):
     """Every tile of the split fp32 convolution (lattices made for few and for
-    many points): ordinary rows; then infinities, NaN and values of 1e30 (the
-    split's sums overflow from 1.2e24 on), which are computed again on fp32
-    matrix instructions and agree where the sum of the same products is
-    finite, infinite or NaN."""
-    w = random_cloud(1500, 3, seed=1500, extent=1.0, C=1)
-    L = _lattice(3, 0.25, bound)
+    many points) and the fp32 tiles that the same launch takes when there are
+    few vertices (up to 64 per CU, of 32 and 48 channels 256): ordinary rows;
+    then infinities, NaN and values of 1e30 (the split's sums overflow from
+    1.2e24 on), which are computed again on fp32 matrix instructions and agree
+    where the sum of the same products is finite, infinite or NaN."""
+    w = random_cloud(points, 3, seed=1500, extent=1.0, C=1)
+    sigma = 0.02 if points > 1500 else 0.25
+    L = _lattice(3, sigma, bound)
     g = GpuLattice(L, w.pos, w.feat)
-    lat = O.build(w.pos, 0.25)
+    lat = O.build(w.pos, sigma)
+    per_cu = 256 if C_out < 64 else 64
+    assert (lat.V > per_cu * torch.cuda.get_device_properties(0).multi_processor_count) == (points > 1500)
     nbr = O.neighbors(lat)
     x = random_rows(lat.V, C_in, seed=1501)
     W = conv_weight(C_in, C_out, 3, seed=1502)
